@@ -57,6 +57,41 @@ bool fop_ok(const hs_plan* p, const void* fop, int64_t ld, int64_t N)
     return ld % ld_align(p->dtype) == 0;
 }
 
+// Strip order of the detection kernels for one FOP of n_strips strips (the
+// kernel side is described in hs_walk_impl.h).  Strip x >= 8 lies in
+// octave L = floor(log2 x) at position (x - 2^L) / 2^L; its list is the three
+// bits after the leading one, and dividing x by 2, 4 or 8 keeps both the list
+// and the position scaled to the top octave.  Strips are ordered by that
+// position, then by octave (x/8, x/4, x/2 just before x), then by index.
+// lists == 8: one list per XCD; lists == 1: one list of all strips.
+// The order is that of walking the binary tree in which x has the children
+// 2x and 2x + 1, each strip followed by all it is an ancestor of, from the
+// eight roots 8 .. 15 (list 1: the roots' trees advance together).
+std::vector<std::vector<uint32_t>> walk_strip_lists(int64_t n_strips, int lists, bool linear = false)
+{
+    std::vector<std::vector<uint32_t>> out(lists);
+    if (n_strips < 1) return out;
+    if (linear) {
+        // increasing strip order, dealt to the lists in turn
+        for (int64_t x = 0; x < n_strips; ++x) out[x % lists].push_back((uint32_t)x);
+        return out;
+    }
+    for (int64_t x = 0; x < n_strips && x < 8; ++x) out[lists == 8 ? x : 0].push_back((uint32_t)x);
+    int top = 3;
+    while (((int64_t)2 << top) <= n_strips - 1) ++top;      // octave of the last strip
+    // positions p of the top octave's sub-ranges in order; the strips at
+    // position p are those of the octaves whose step divides it
+    for (int64_t p = 0; p < ((int64_t)1 << (top - 3)); ++p) {
+        const int lo = p == 0 ? 3 : top - __builtin_ctzll((uint64_t)p);
+        for (int k = 0; k < 8; ++k)
+            for (int L = lo < 3 ? 3 : lo; L <= top; ++L) {
+                const int64_t x = ((int64_t)1 << L) + ((int64_t)k << (L - 3)) + (p >> (top - L));
+                if (x < n_strips) out[lists == 8 ? k : 0].push_back((uint32_t)x);
+            }
+    }
+    return out;
+}
+
 // Full-tile schedule of a single-FOP plan (the kernel side is described in
 // hs_fused_impl.h).  Bin tile x >= 8 lies in octave L = floor(log2 x); list
 // k holds the tiles whose bits L-1..L-3 equal k (tiles 0..7 go to list x),
@@ -68,120 +103,82 @@ std::vector<uint32_t> build_schedule(int64_t n_full, int row_blocks)
 {
     std::vector<uint32_t> out;
     if (n_full < 1 || row_blocks < 1 || row_blocks > 255 || n_full >= ((int64_t)1 << 24)) return out;
-    int top = 0;
-    while (((int64_t)2 << top) <= n_full - 1) ++top;      // floor(log2(n_full - 1)), 0 for n_full <= 2
-    struct E { int64_t key; int L; int64_t x; };
-    std::vector<E> lists[8];
-    for (int64_t x = 0; x < n_full; ++x) {
-        if (x < 8) {
-            lists[x].push_back({0, -1, x});
-            continue;
-        }
-        int L = 3;
-        while (((int64_t)2 << L) <= x) ++L;
-        const int64_t off = x - ((int64_t)1 << L);
-        const int k = (int)(off >> (L - 3));
-        const int64_t pos = off & (((int64_t)1 << (L - 3)) - 1);
-        lists[k].push_back({pos << (top - L), L, x});
-    }
+    const auto lists = walk_strip_lists(n_full, 8);
+    out.reserve(9 + (size_t)n_full * row_blocks);
     out.assign(9, 0);
-    for (int k = 0; k < 8; ++k) {
-        std::sort(lists[k].begin(), lists[k].end(), [](const E& a, const E& b) {
-            if (a.key != b.key) return a.key < b.key;
-            if (a.L != b.L) return a.L < b.L;
-            return a.x < b.x;
-        });
-        out[k + 1] = out[k] + (uint32_t)(lists[k].size() * row_blocks);
-    }
+    for (int k = 0; k < 8; ++k) out[k + 1] = out[k] + (uint32_t)(lists[k].size() * row_blocks);
     for (int k = 0; k < 8; ++k)
-        for (const E& e : lists[k])
-            for (int rb = 0; rb < row_blocks; ++rb) out.push_back(((uint32_t)rb << 24) | (uint32_t)e.x);
+        for (uint32_t x : lists[k])
+            for (int rb = 0; rb < row_blocks; ++rb) out.push_back(((uint32_t)rb << 24) | x);
     return out;
 }
 
-// Strip order of the walk kernel for one FOP of n_strips strips of 256 bins
-// (the kernel side is described in hs_walk_impl.h).  Strip x >= 8 lies in
-// octave L = floor(log2 x) at position (x - 2^L) / 2^L; its list is the three
-// bits after the leading one, and dividing x by 2, 4 or 8 keeps both the list
-// and the position scaled to the top octave.  Strips are ordered by that
-// position, then by octave (x/8, x/4, x/2 just before x), then by index.
-// lists == 8: one list per XCD; lists == 1: one list of all strips.
-std::vector<std::vector<uint32_t>> walk_strip_lists(int64_t n_strips, int lists, bool linear = false)
+// A run of `count` units of FOP f from entry `first` of the unit list.
+struct Run {
+    int32_t f;
+    int64_t first, count;
+};
+
+// The runs dealt to each XCD, evened out: XCDs with more than an eighth of
+// the units hand their last ones to those with fewer.  (Bin counts that are
+// no power of two leave the octave lists uneven, and few FOPs the batch's.)
+void even_runs(std::vector<Run> (&on)[8])
 {
-    std::vector<std::vector<uint32_t>> out(lists);
-    if (n_strips < 1) return out;
-    if (linear) {
-        // increasing strip order, dealt to the lists in turn
-        for (int64_t x = 0; x < n_strips; ++x) out[x % lists].push_back((uint32_t)x);
-        return out;
+    int64_t total = 0, has[8];
+    for (int x = 0; x < 8; ++x) {
+        has[x] = 0;
+        for (const Run& r : on[x]) has[x] += r.count;
+        total += has[x];
     }
-    int top = 0;
-    while (((int64_t)2 << top) <= n_strips - 1) ++top;
-    struct E { int64_t key; int L; int64_t x; };
-    std::vector<E> l[8];
-    for (int64_t x = 0; x < n_strips; ++x) {
-        if (x < 8) {
-            l[lists == 8 ? x : 0].push_back({0, -1, x});
-            continue;
+    const int64_t quota = (total + 7) / 8;
+    std::vector<Run> pool;
+    for (int x = 0; x < 8; ++x) {
+        while (has[x] > quota) {
+            Run& r = on[x].back();
+            const int64_t n = std::min(r.count, has[x] - quota);
+            pool.push_back({r.f, r.first + r.count - n, n});
+            r.count -= n;
+            has[x] -= n;
+            if (r.count == 0) on[x].pop_back();
         }
-        int L = 3;
-        while (((int64_t)2 << L) <= x) ++L;
-        const int64_t off = x - ((int64_t)1 << L);
-        const int k = (int)(off >> (L - 3));
-        const int64_t pos = off & (((int64_t)1 << (L - 3)) - 1);
-        l[lists == 8 ? k : 0].push_back({(pos << (top - L)) << 3 | k, L, x});
     }
-    for (int k = 0; k < lists; ++k) {
-        std::sort(l[k].begin(), l[k].end(), [](const E& a, const E& b) {
-            if (a.key != b.key) return a.key < b.key;
-            if (a.L != b.L) return a.L < b.L;
-            return a.x < b.x;
-        });
-        for (const E& e : l[k]) out[k].push_back((uint32_t)e.x);
+    size_t q = 0;
+    for (int x = 0; x < 8 && q < pool.size(); ++x) {
+        while (has[x] < quota && q < pool.size()) {
+            Run& r = pool[q];
+            const int64_t n = std::min(r.count, quota - has[x]);
+            on[x].push_back({r.f, r.first, n});
+            r.first += n;
+            r.count -= n;
+            has[x] += n;
+            if (r.count == 0) ++q;
+        }
     }
-    return out;
 }
 
-// Walk tables of a plan: units (band << 24) | strip for every band of every
-// strip; a single FOP spreads its strips over eight XCD lists, a batch puts
-// each FOP whole on one XCD (longest first onto the least loaded XCD).
-// Device layout: xseg [9] u32 | rowmask [T] u32 | seg [n_seg][4] i32 |
-// n_chans [n_fops] i64 | entries u32.
-void build_walk(hs_plan* p, bool linear)
+// Detection units of a plan: the strips of every FOP (64 V bins; 256-bin
+// tiles for the tile kernel).  A single FOP spreads its strips over eight XCD
+// lists, a batch puts each FOP whole on one XCD (longest first onto the least
+// loaded XCD); the lists are then evened out.
+// Device layout: xseg [9] u32 | seg [n_seg][4] i32 | n_chans [n_fops] i64 |
+// entries u32.
+void build_units(hs_plan* p, bool walk, bool linear)
 {
-    const int T = (int)p->T;
-    const int c = T / 2;
-    // the two half-planes as bands when each has at least kWalkDepth rows
-    // (the kernel keeps that many rows in flight and starts at most one unit
-    // inside them), else the full height as one band
-    p->band_split = (c >= hsk::kWalkDepth && T - c >= hsk::kWalkDepth) ? c : 0;
-    const int bands = p->band_split > 0 ? 2 : 1;
-    std::vector<uint32_t> rowmask(T, 0u);
-    for (int r = 0; r < T; ++r)
-        for (int m = 2; m <= hsk::kMaxH; ++m)
-            if (((r - c) % m + m) % m == 0) rowmask[r] |= 1u << m;
-
+    const int64_t sb = walk ? 64 * (int64_t)p->walk_v : hsk::kTileBins;
     std::vector<uint32_t> ent;
-    std::vector<int32_t> seg;   // 4 per segment
-    std::vector<uint32_t> xseg(9, 0);
     auto add_units = [&](const std::vector<uint32_t>& strips) {
         const size_t first = ent.size();
-        for (int b = 0; b < bands; ++b)
-            for (uint32_t x : strips) ent.push_back(((uint32_t)b << 24) | x);
-        return std::make_pair((int64_t)first, (int64_t)(ent.size() - first));
+        ent.insert(ent.end(), strips.begin(), strips.end());
+        return std::make_pair((int64_t)first, (int64_t)strips.size());
     };
+    std::vector<Run> on[8];
     std::vector<int64_t> nchan;
     if (p->n_fops == 0) {
-        const int64_t sb = 64 * (int64_t)p->walk_v;
         const auto lists = walk_strip_lists((p->N + sb - 1) / sb, 8, linear);
         for (int x = 0; x < 8; ++x) {
-            xseg[x] = (uint32_t)(seg.size() / 4);
             const auto r = add_units(lists[x]);
-            if (r.second > 0) {
-                seg.insert(seg.end(), {0, (int32_t)r.first, 0, (int32_t)r.second});
-            }
+            if (r.second > 0) on[x].push_back({0, r.first, r.second});
         }
-        xseg[8] = (uint32_t)(seg.size() / 4);
     } else {
         // one unit list per distinct length
         std::vector<std::pair<int64_t, std::pair<int64_t, int64_t>>> by_len;   // N -> (first, count)
@@ -190,7 +187,6 @@ void build_walk(hs_plan* p, bool linear)
             const int64_t n = p->n_chans[f];
             auto it = std::find_if(by_len.begin(), by_len.end(), [&](const auto& e) { return e.first == n; });
             if (it == by_len.end()) {
-                const int64_t sb = 64 * (int64_t)p->walk_v;
                 const auto lists = walk_strip_lists((n + sb - 1) / sb, 1, linear);
                 by_len.push_back({n, add_units(lists[0])});
                 it = by_len.end() - 1;
@@ -201,50 +197,66 @@ void build_walk(hs_plan* p, bool linear)
         std::vector<int> order(p->n_fops);
         for (int f = 0; f < p->n_fops; ++f) order[f] = f;
         std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return fl[a].second > fl[b].second; });
-        std::vector<std::vector<int>> on(8);
+        std::vector<int> to(p->n_fops);
         int64_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (int f : order) {
             int best = 0;
             for (int x = 1; x < 8; ++x)
                 if (load[x] < load[best]) best = x;
-            on[best].push_back(f);
+            to[f] = best;
             load[best] += fl[f].second;
         }
-        for (int x = 0; x < 8; ++x) {
-            std::sort(on[x].begin(), on[x].end());
-            xseg[x] = (uint32_t)(seg.size() / 4);
-            int64_t pre = 0;
-            for (int f : on[x]) {
-                if (fl[f].second == 0) continue;
-                seg.insert(seg.end(), {(int32_t)f, (int32_t)fl[f].first, (int32_t)pre, (int32_t)(pre + fl[f].second)});
-                pre += fl[f].second;
-            }
-        }
-        xseg[8] = (uint32_t)(seg.size() / 4);
+        for (int f = 0; f < p->n_fops; ++f)
+            if (fl[f].second > 0) on[to[f]].push_back({(int32_t)f, fl[f].first, fl[f].second});
         nchan = p->n_chans;
     }
+    even_runs(on);
+    if (p->n_fops == 0) {
+        // one contiguous run of entries per XCD
+        std::vector<uint32_t> all;
+        all.reserve(ent.size());
+        for (int x = 0; x < 8; ++x) {
+            const size_t first = all.size();
+            for (const Run& r : on[x]) all.insert(all.end(), ent.begin() + r.first, ent.begin() + r.first + r.count);
+            p->xfirst[x] = (int32_t)first;
+            p->xcount[x] = (int32_t)(all.size() - first);
+            on[x].clear();
+            if (all.size() > first) on[x].push_back({0, (int64_t)first, (int64_t)(all.size() - first)});
+        }
+        ent.swap(all);
+    }
+
+    std::vector<int32_t> seg;   // 4 per segment: FOP, first entry, first index, end index
+    std::vector<uint32_t> xseg(9, 0);
+    p->walk_units = 0;
+    for (int x = 0; x < 8; ++x) {
+        xseg[x] = (uint32_t)(seg.size() / 4);
+        int64_t pre = 0;
+        for (const Run& r : on[x]) {
+            seg.insert(seg.end(), {r.f, (int32_t)r.first, (int32_t)pre, (int32_t)(pre + r.count)});
+            pre += r.count;
+        }
+        p->walk_units = std::max(p->walk_units, pre);
+    }
+    xseg[8] = (uint32_t)(seg.size() / 4);
 
     auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
     p->off_xseg = 0;
-    p->off_rowmask = align(p->off_xseg + xseg.size() * 4);
-    p->off_seg = align(p->off_rowmask + rowmask.size() * 4);
+    p->off_seg = align(p->off_xseg + xseg.size() * 4);
     p->off_nchan = align(p->off_seg + seg.size() * 4);
     p->off_ent = align(p->off_nchan + nchan.size() * 8);
     p->walk_tab.assign(align(p->off_ent + ent.size() * 4), 0);
     std::memcpy(p->walk_tab.data() + p->off_xseg, xseg.data(), xseg.size() * 4);
-    std::memcpy(p->walk_tab.data() + p->off_rowmask, rowmask.data(), rowmask.size() * 4);
     if (!seg.empty()) std::memcpy(p->walk_tab.data() + p->off_seg, seg.data(), seg.size() * 4);
     if (!nchan.empty()) std::memcpy(p->walk_tab.data() + p->off_nchan, nchan.data(), nchan.size() * 8);
     if (!ent.empty()) std::memcpy(p->walk_tab.data() + p->off_ent, ent.data(), ent.size() * 4);
-    p->walk_lds = hsk::walk_lds_bytes(T, p->H, p->dtype, p->walk_v);
-    p->walk = true;
+    p->walk = walk;
 }
 
 // Device copies of a plan's tables on one device.
 struct DevTabs {
-    const unsigned char* walk = nullptr;   // strip-walk units and row table
+    const unsigned char* walk = nullptr;   // detection units
     const uint32_t* sched = nullptr;       // full-tile schedule (null: contiguous chunks)
-    const int64_t* batch = nullptr;        // batched: bins of each FOP, then the tile prefix
 };
 
 hs_status copy_to_device(const void* src, size_t bytes, void** dst)
@@ -275,10 +287,9 @@ hs_status device_tables(const hs_plan* p, hipStream_t stream, DevTabs* t)
         if (hipStreamGetDevice(stream, &sd) != hipSuccess || (int)sd != dev) return HS_ERR_INVALID;
     }
     std::lock_guard<std::mutex> g(p->mu);
-    const bool need_walk = p->walk && !p->d_walk[dev];
+    const bool need_walk = !p->walk_tab.empty() && !p->d_walk[dev];
     const bool need_sched = !p->sched.empty() && !p->d_sched[dev];
-    const bool need_batch = p->n_fops > 0 && !p->d_tables[dev];
-    if (need_walk || need_sched || need_batch) {
+    if (need_walk || need_sched) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &cs) != hipSuccess) return HS_ERR_HIP;
         if (cs != hipStreamCaptureStatusNone) return HS_ERR_INVALID;
@@ -293,18 +304,9 @@ hs_status device_tables(const hs_plan* p, hipStream_t stream, DevTabs* t)
             if (st != HS_OK) return st;
             p->d_sched[dev] = static_cast<uint32_t*>(d);
         }
-        if (need_batch) {
-            std::vector<int64_t> h((size_t)p->n_fops * 2 + 1);
-            for (int f = 0; f < p->n_fops; ++f) h[f] = p->n_chans[f];
-            for (int f = 0; f <= p->n_fops; ++f) h[p->n_fops + f] = p->tile_prefix[f];
-            const hs_status st = copy_to_device(h.data(), h.size() * sizeof(int64_t), &d);
-            if (st != HS_OK) return st;
-            p->d_tables[dev] = static_cast<int64_t*>(d);
-        }
     }
     t->walk = p->d_walk[dev];
     t->sched = p->d_sched[dev];
-    t->batch = p->d_tables[dev];
     return HS_OK;
 }
 
@@ -323,7 +325,6 @@ hs_status device_tables_present(const hs_plan* p, hipStream_t stream, DevTabs* t
     std::lock_guard<std::mutex> g(p->mu);
     t->walk = p->d_walk[dev];
     t->sched = p->d_sched[dev];
-    t->batch = p->d_tables[dev];
     return HS_OK;
 }
 
@@ -332,17 +333,27 @@ hsk::WalkArgs walk_args(const hs_plan* p, const unsigned char* tab)
     hsk::WalkArgs a{};
     a.T = (int32_t)p->T;
     a.c = (int32_t)(p->T / 2);
-    a.band_split = p->band_split;
     a.scale = p->scale;
     a.inv_scale = 1.0f / p->scale;
     a.s_row = p->s_row;
     a.s_bin = p->s_bin;
     a.xseg = reinterpret_cast<const uint32_t*>(tab + p->off_xseg);
-    a.rowmask = reinterpret_cast<const uint32_t*>(tab + p->off_rowmask);
+    a.units_per_list = p->walk_units;
+    std::memcpy(a.xfirst, p->xfirst, sizeof(a.xfirst));
+    std::memcpy(a.xcount, p->xcount, sizeof(a.xcount));
+    a.lim_rows = p->walk ? (int32_t)p->T : hsk::stage_rows(2);
+    a.lim_bins = p->walk ? 0 : hsk::kTileBins;
     a.seg = reinterpret_cast<const int32_t*>(tab + p->off_seg);
     a.n_chans = reinterpret_cast<const int64_t*>(tab + p->off_nchan);
     a.ent = reinterpret_cast<const uint32_t*>(tab + p->off_ent);
     return a;
+}
+
+// The plan's detection kernel.
+hipError_t launch_detect(const hs_plan* p, const hsk::WalkArgs& a, hipStream_t s)
+{
+    return p->walk ? hsk::launch_walk(p->dtype, p->H, p->walk_v, a, p->persistent_blocks, s)
+                   : hsk::launch_tiles(p->dtype, p->H, a, p->persistent_blocks, s);
 }
 
 hsk::FracArgs frac_args(const hs_plan* p, const void* fop, int64_t ld)
@@ -376,7 +387,6 @@ hsk::TileArgs tile_args(const hs_plan* p, const void* fop, int64_t ld, const Dev
     a.inv_scale = 1.0f / p->scale;
     a.s_row = p->s_row;
     a.s_bin = p->s_bin;
-    a.kmask = (1u << p->s_k) - 1u;
     a.table_whole = hsk::table_whole((int)p->T, p->H) ? 1 : 0;
     a.sched = t.sched;
     return a;
@@ -471,22 +481,18 @@ hs_status hs_plan_create(hs_plan** out, const hs_plan_desc* d)
         const bool walk_wins = p->dtype != HS_DTYPE_F32 || p->H > 8;
         const bool want_walk = d->schedule == 1 || d->schedule == 4 || (d->schedule == 0 && walk_wins);
         const bool paper = d->mapping == HS_MAP_PAPER;   // the fractional mapping has a kernel of its own
-        if (paper && want_walk && hsk::walk_supported((int)p->T, p->H)) build_walk(p, d->schedule == 1);
+        const bool walk = paper && want_walk && hsk::walk_supported((int)p->T, p->H);
 
         if (d->n_fops == 0) {
             p->tiles_total = p->row_blocks * bin_tiles(p->N);
             if (paper && (d->schedule == 0 || d->schedule == 2 || d->schedule == 4))
                 p->sched = build_schedule(p->N / hsk::kTileBins, p->row_blocks);
         } else {
-            p->tile_prefix.resize(d->n_fops + 1);
             int64_t acc = 0;
-            for (int f = 0; f < d->n_fops; ++f) {
-                p->tile_prefix[f] = acc;
-                acc += p->row_blocks * bin_tiles(p->n_chans[f]);
-            }
-            p->tile_prefix[d->n_fops] = acc;
+            for (int64_t n : p->n_chans) acc += p->row_blocks * bin_tiles(n);
             p->tiles_total = acc;
         }
+        if (paper) build_units(p, walk, d->schedule == 1 || d->schedule == 3);
         *out = p;
         return HS_OK;
     } catch (const std::bad_alloc&) {
@@ -502,9 +508,8 @@ hs_status hs_plan_destroy(hs_plan* p)
     int cur = -1;
     bool have_dev = hipGetDevice(&cur) == hipSuccess;
     for (int dev = 0; dev < 64; ++dev) {
-        if (p->d_tables[dev] || p->d_sched[dev] || p->d_walk[dev]) {
+        if (p->d_sched[dev] || p->d_walk[dev]) {
             if (have_dev) (void)hipSetDevice(dev);
-            if (p->d_tables[dev]) (void)hipFree(p->d_tables[dev]);
             if (p->d_sched[dev]) (void)hipFree(p->d_sched[dev]);
             if (p->d_walk[dev]) (void)hipFree(p->d_walk[dev]);
         }
@@ -608,7 +613,7 @@ hs_status hs_detect(const hs_plan* p, const void* fop, int64_t ld, const float* 
             a.cap = capacity;
             a.counts = reinterpret_cast<unsigned long long*>(counts);
             if (hsk::launch_frac(p->dtype, true, a, s) != hipSuccess) return HS_ERR_HIP;
-        } else if (p->walk) {
+        } else {
             if (hsk::launch_zero_i64(counts, p->H + 1, s) != hipSuccess) return HS_ERR_HIP;
             hsk::WalkArgs a = walk_args(p, t.walk);
             a.fop = fop;
@@ -619,21 +624,9 @@ hs_status hs_detect(const hs_plan* p, const void* fop, int64_t ld, const float* 
             a.out = out;
             a.cap = capacity;
             a.counts = reinterpret_cast<unsigned long long*>(counts);
-            if (hsk::launch_walk(p->dtype, p->H, p->walk_v, a, p->persistent_blocks, p->walk_lds, s) != hipSuccess)
-                return HS_ERR_HIP;
-        } else {
-            hipError_t e = hsk::launch_zero_i64(counts, p->H + 1, s);
-            if (e != hipSuccess) return HS_ERR_HIP;
-            hsk::TileArgs a = tile_args(p, fop, ld, t);
-            a.ta = ta;
-            a.out = out;
-            a.cap = capacity;
-            a.counts = reinterpret_cast<unsigned long long*>(counts);
-            if (hsk::launch_fused(hsk::kModeDetect, p->dtype, p->H, a, p->tiles_total,
-                                  persistent_grid(p, p->tiles_total), p->lds_bytes, s) != hipSuccess)
-                return HS_ERR_HIP;
+            if (launch_detect(p, a, s) != hipSuccess) return HS_ERR_HIP;
         }
-        if (capacity == 0) return HS_OK;
+        if (p->mapping != HS_MAP_FRACTIONAL || capacity == 0) return HS_OK;
         return from_hip(hsk::launch_plane_counts(out, nullptr, nullptr, capacity,
                                                  reinterpret_cast<unsigned long long*>(counts), 1, p->H,
                                                  p->s_bin, (1u << p->s_k) - 1u, s));
@@ -728,53 +721,17 @@ hs_status hs_detect_batched(const hs_plan* p, const void* const* fops, const int
         DevTabs t;
         const hs_status st = device_tables(p, s, &t);
         if (st != HS_OK) return st;
-        if (p->walk) {
-            if (hsk::launch_zero_i64(counts, (int64_t)p->n_fops * (p->H + 1), s) != hipSuccess) return HS_ERR_HIP;
-            hsk::WalkArgs a = walk_args(p, t.walk);
-            a.n_fops = p->n_fops;
-            a.fops = fops;
-            a.lds = lds;
-            a.out_offsets = out_offsets;
-            a.caps = caps;
-            a.ta = ta;
-            a.out = out;
-            a.counts = reinterpret_cast<unsigned long long*>(counts);
-            if (hsk::launch_walk(p->dtype, p->H, p->walk_v, a, p->persistent_blocks, p->walk_lds, s) != hipSuccess)
-                return HS_ERR_HIP;
-            return from_hip(hsk::launch_plane_counts(out, out_offsets, caps, 0,
-                                                     reinterpret_cast<unsigned long long*>(counts), p->n_fops,
-                                                     p->H, p->s_bin, (1u << p->s_k) - 1u, s));
-        }
-        const int64_t* tables = t.batch;
-        hipError_t e = hsk::launch_zero_i64(counts, (int64_t)p->n_fops * (p->H + 1), s);
-        if (e != hipSuccess) return HS_ERR_HIP;
-        hsk::BatchArgs b{};
-        b.fops = fops;
-        b.lds = lds;
-        b.n_chans = tables;
-        b.tile_prefix = tables + p->n_fops;
-        b.tiles_total = p->tiles_total;
-        b.n_fops = p->n_fops;
-        b.T = (int32_t)p->T;
-        b.c = (int32_t)(p->T / 2);
-        b.R = p->tile_rows;
-        b.row_blocks = p->row_blocks;
-        b.scale = p->scale;
-        b.inv_scale = 1.0f / p->scale;
-        b.ta = ta;
-        b.out = out;
-        b.out_offsets = out_offsets;
-        b.caps = caps;
-        b.counts = reinterpret_cast<unsigned long long*>(counts);
-        b.s_row = p->s_row;
-        b.s_bin = p->s_bin;
-        b.kmask = (1u << p->s_k) - 1u;
-        b.table_whole = hsk::table_whole((int)p->T, p->H) ? 1 : 0;
-        const int grid = persistent_grid(p, p->tiles_total);
-        if (hsk::launch_batched(p->dtype, p->H, b, grid, p->lds_bytes, s) != hipSuccess) return HS_ERR_HIP;
-        return from_hip(hsk::launch_plane_counts(out, out_offsets, caps, 0,
-                                                 reinterpret_cast<unsigned long long*>(counts), p->n_fops, p->H,
-                                                 p->s_bin, b.kmask, s));
+        if (hsk::launch_zero_i64(counts, (int64_t)p->n_fops * (p->H + 1), s) != hipSuccess) return HS_ERR_HIP;
+        hsk::WalkArgs a = walk_args(p, t.walk);
+        a.n_fops = p->n_fops;
+        a.fops = fops;
+        a.lds = lds;
+        a.out_offsets = out_offsets;
+        a.caps = caps;
+        a.ta = ta;
+        a.out = out;
+        a.counts = reinterpret_cast<unsigned long long*>(counts);
+        return from_hip(launch_detect(p, a, s));
     } catch (...) {
         return HS_ERR_HIP;
     }

@@ -9,7 +9,7 @@ namespace hsk {
 #define HS_DECL_GROUP(n, g)                                                                     \
     hipError_t launch_fused_##n##_g##g(int mode, int H, const TileArgs& a, int64_t nt, int grid,  \
                                        int lds, hipStream_t s);                                  \
-    hipError_t launch_batched_##n##_g##g(int H, const BatchArgs& b, int grid, int lds, hipStream_t s);
+    hipError_t launch_tiles_##n##_g##g(int H, const WalkArgs& a, int grid, hipStream_t s);
 #define HS_DECL_TYPE(n) HS_DECL_GROUP(n, 0) HS_DECL_GROUP(n, 1) HS_DECL_GROUP(n, 2) HS_DECL_GROUP(n, 3)
 HS_DECL_TYPE(f32)
 HS_DECL_TYPE(f16)
@@ -138,22 +138,22 @@ hipError_t launch_fused(int mode, int dtype, int H, const TileArgs& a, int64_t n
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_batched(int dtype, int H, const BatchArgs& b, int grid, int lds_bytes, hipStream_t s)
+hipError_t launch_tiles(int dtype, int H, const WalkArgs& a, int grid, hipStream_t s)
 {
     if (H < 1 || H > kMaxH) return hipErrorInvalidValue;
     switch (dtype) {
     case HS_DTYPE_F32: {
-#define HS_CALL(g) launch_batched_f32_g##g(H, b, grid, lds_bytes, s)
+#define HS_CALL(g) launch_tiles_f32_g##g(H, a, grid, s)
         HS_GROUP_CASES(HS_CALL)
 #undef HS_CALL
     }
     case HS_DTYPE_F16: {
-#define HS_CALL(g) launch_batched_f16_g##g(H, b, grid, lds_bytes, s)
+#define HS_CALL(g) launch_tiles_f16_g##g(H, a, grid, s)
         HS_GROUP_CASES(HS_CALL)
 #undef HS_CALL
     }
     case HS_DTYPE_BF16: {
-#define HS_CALL(g) launch_batched_bf16_g##g(H, b, grid, lds_bytes, s)
+#define HS_CALL(g) launch_tiles_bf16_g##g(H, a, grid, s)
         HS_GROUP_CASES(HS_CALL)
 #undef HS_CALL
     }

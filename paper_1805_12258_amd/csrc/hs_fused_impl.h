@@ -37,13 +37,9 @@
 
 #include <type_traits>
 
-#include "hs_internal.h"
+#include "hs_rows.h"
 
 namespace hsk {
-
-struct bf16_t {
-    uint16_t bits;
-};
 
 template <typename TIn> struct Io;
 
@@ -144,23 +140,8 @@ struct Smem {
     float* rowtab[2];             // per row: staged-row offsets of m = 2..H, then
                                   // the H thresholds (both entries alias when the
                                   // table covers the whole plane)
-    uint64_t* cand;               // [kWaves][kWaveCandCap] per-wave candidate buffers
-                                  // (bin word in the low half, power bits high)
-    int* cnt;                     // [kCntWords] bookkeeping of the block's candidate flush
-    struct FlushParams* fp;       // where flushed candidates go
+    float* pairs;                 // [kWaves][H][2] the waves' pairs (log-sum-exp)
 };
-
-// Candidate output of the FOP being processed, kept in LDS so that the
-// out-of-line flush needs only LDS pointers (few registers at the call).
-struct FlushParams {
-    hs_cand* out;
-    int64_t cap;
-    unsigned long long* counts;   // [H+1]: per-plane counts, then the total
-    int32_t H;
-    int32_t s_bin;
-    uint32_t kmask;
-};
-static_assert(sizeof(FlushParams) <= kFlushParamBytes, "flush parameters");
 
 template <int H, int EB>
 __device__ __forceinline__ Smem carve(float* lds, int T, int R, bool whole)
@@ -182,18 +163,15 @@ __device__ __forceinline__ Smem carve(float* lds, int T, int R, bool whole)
     s.rowtab[0] = tab;
     const int trows = whole ? T : R;
     s.rowtab[1] = whole ? s.rowtab[0] : s.rowtab[0] + trows * row_table_stride(H);
-    s.cand = reinterpret_cast<uint64_t*>(s.rowtab[1] + trows * row_table_stride(H));
-    s.cnt = reinterpret_cast<int*>(s.cand + kWaves * kWaveCandCap);
-    s.fp = reinterpret_cast<FlushParams*>(s.cnt + kCntWords);
+    s.pairs = s.rowtab[1] + trows * row_table_stride(H);
     return s;
 }
 
-// Per-wave detection state (a wave-uniform value).
+// The log-sum-exp's state of a lane.
 template <int H>
 struct WaveState {
-    int n;          // detection: entries in the wave's LDS buffer (wave-uniform)
-    float lm[H];    // log-sum-exp: the lane's running maximum of each plane
-    float ls[H];    //   and the sum of exp2((x - lm) * lse_c) over its values
+    float lm[H];    // running maximum of each plane
+    float ls[H];    // and the sum of exp2((x - lm) * lse_c) over its values
 };
 
 // Merge two (max, sum) pairs of the log-sum-exp in fp32.  A pair with max
@@ -228,124 +206,6 @@ __device__ __forceinline__ void lse_add(const float (&x)[V], float& M, float& S,
 #pragma unroll
         for (int v = 0; v < V; ++v) t = t + __builtin_amdgcn_exp2f((x[v] - base) * c);
         S = S + t;
-    }
-}
-
-__device__ __forceinline__ uint64_t read_first_u64(uint64_t x)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
-// Write a wave's buffered candidates to global memory (one atomic per wave
-// reserves their positions in the list).  The per-plane counts of the
-// entries that fit are formed afterwards from the list itself (a counting
-// pass); entries past the capacity are dropped, and only those are counted
-// here, per plane.
-__device__ __forceinline__ void store_cands(const uint64_t* wbuf, int n, unsigned long long base, hs_cand* out,
-                                            int64_t cap, unsigned long long* counts, int s_bin, uint32_t kmask)
-{
-    const int lane = threadIdx.x & 63;
-    for (int e0 = 0; e0 < n; e0 += 64) {   // uniform trip count
-        const int e = e0 + lane;
-        if (e < n) {
-            const uint64_t c = wbuf[e];
-            if ((int64_t)(base + e) < cap) reinterpret_cast<uint64_t*>(out)[base + e] = c;
-            else atomicAdd(&counts[((uint32_t)c >> s_bin) & kmask], 1ull);
-        }
-    }
-}
-
-__device__ __forceinline__ void flush_wave(const uint64_t* wbuf, int n, hs_cand* out, int64_t cap,
-                                           unsigned long long* counts, int H, int s_bin, uint32_t kmask)
-{
-    const int lane = threadIdx.x & 63;
-    unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(&counts[H], (unsigned long long)n);
-    base = read_first_u64(base);
-    store_cands(wbuf, n, base, out, cap, counts, s_bin, kmask);
-}
-
-// Flush every wave's buffer with one atomic for the whole block (called by
-// the whole block; contains barriers).  `n` is the calling wave's fill; the
-// block's bookkeeping uses the LDS words at sh.cnt.
-template <int H>
-__device__ __forceinline__ void flush_block(const Smem& sh, int n, unsigned long long* counts, hs_cand* out,
-                                            int64_t cap, int s_bin, uint32_t kmask)
-{
-    int* bf = sh.cnt;   // [0, kWaves): fills; [kWaves, 2 kWaves): offsets; then the base (2 words)
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) bf[wave] = n;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            bf[kWaves + w] = acc;
-            acc += bf[w];
-        }
-        const unsigned long long b = acc ? atomicAdd(&counts[H], (unsigned long long)acc) : 0ull;
-        bf[2 * kWaves] = (int)(uint32_t)b;
-        bf[2 * kWaves + 1] = (int)(uint32_t)(b >> 32);
-    }
-    __syncthreads();
-    const unsigned long long base = ((unsigned long long)(uint32_t)bf[2 * kWaves + 1] << 32) |
-                                    (uint32_t)bf[2 * kWaves];
-    store_cands(sh.cand + wave * kWaveCandCap, n, base + (unsigned long long)bf[kWaves + wave], out, cap, counts,
-                s_bin, kmask);
-    __syncthreads();
-}
-
-// Out-of-line flush of the calling wave's buffer (n entries): the rare path
-// inside the row loop, kept out of line so the loop stays small.
-__device__ __noinline__ void flush_call(int n, const uint64_t* wbuf, const FlushParams* fp)
-{
-    flush_wave(wbuf, n, fp->out, fp->cap, fp->counts, fp->H, fp->s_bin, fp->kmask);
-}
-
-__device__ __forceinline__ void set_flush_params(const Smem& sh, hs_cand* out, int64_t cap,
-                                                 unsigned long long* counts, int H, int s_bin, uint32_t kmask)
-{
-    if (threadIdx.x == 0) {
-        sh.fp->out = out;
-        sh.fp->cap = cap;
-        sh.fp->counts = counts;
-        sh.fp->H = H;
-        sh.fp->s_bin = s_bin;
-        sh.fp->kmask = kmask;
-    }
-}
-
-// Append the hits of one (row, plane) to the wave's LDS buffer.  Called by
-// the whole wave (uniform control flow): positions come from wave ballots.
-// `lanes` is the number of lanes with a hit: the call adds at most V * lanes
-// entries.  The buffer is written out only when that many might not fit, so
-// that a flush carries a nearly full buffer (each flush costs one atomic on
-// the list's shared counter).
-template <int V, int H>
-__device__ __forceinline__ void emit_hits(const float* acc, float t, int r, int k, int64_t jb, int lanes,
-                                          const TileArgs& a, const Smem& sh, WaveState<H>& ws,
-                                          uint64_t* wbuf)
-{
-    const uint32_t hi = (uint32_t)(((uint64_t)r << a.s_row) | ((uint64_t)(k - 1) << a.s_bin));
-    static_assert(kWaveCandCap >= V * 64, "candidate buffer");
-    if (__builtin_expect(ws.n + V * lanes > kWaveCandCap, 0)) {
-        flush_call(ws.n, wbuf, sh.fp);
-        ws.n = 0;
-    }
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
-        const bool hit = acc[v] > t;
-        const uint64_t mk = __builtin_amdgcn_ballot_w64(hit);
-        if (mk) {
-            const int pre = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32),
-                                                           __builtin_amdgcn_mbcnt_lo((uint32_t)mk, 0));
-            // sums are in storage units: the reported power is unscaled
-            if (hit)
-                wbuf[ws.n + pre] = ((uint64_t)__float_as_uint(acc[v] * a.inv_scale) << 32) | (hi | (uint32_t)(jb + v));
-            ws.n += __builtin_popcountll(mk);
-        }
     }
 }
 
@@ -555,11 +415,10 @@ __device__ __forceinline__ void issue_tile(const TileArgs& a, const RowGeo& g, i
     }
 
     // 3. Row table of the tile (large planes only): per tile row, where each
-    // stretch factor's source row sits in the staging buffer, and the row's
-    // thresholds.  Per-row scalar work would otherwise dominate the row loop.
+    // stretch factor's source row sits in the staging buffer.  Per-row scalar
+    // work would otherwise dominate the row loop.
     if (!a.table_whole) {
         constexpr int RS = row_table_stride(H);
-        constexpr int SO = row_table_thr_offset(H);
         for (int e = threadIdx.x; e < g.nr * RS; e += kThreads) {
             const int rr = e / RS, col = e - rr * RS;
             const int r = g.r0 + rr;
@@ -573,9 +432,6 @@ __device__ __forceinline__ void issue_tile(const TileArgs& a, const RowGeo& g, i
                               (src_row_lo<m>(r, a.c) - src_row_lo<m>(g.r0, a.c)) * stage_row_words(m);
                 });
                 val = __int_as_float(off);
-            } else if (MODE == kModeDetect && col >= SO && col < SO + H) {
-                // thresholds exist only in the detection mode (a.ta is null otherwise)
-                val = a.ta[(int64_t)(col - SO) * a.T + r] * a.scale;   // storage units (exact)
             }
             rowtab[e] = val;
         }
@@ -598,7 +454,6 @@ __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g,
     const int N = (int)a.N;
     const int jb = j0 + kV * lane;
     constexpr int RS = row_table_stride(H);
-    constexpr int SO = row_table_thr_offset(H);
     const int trow0 = a.table_whole ? r0 : 0;          // table row of tile row 0
 
     // Per-lane view of the staged rows: the lane's first source word of each
@@ -613,7 +468,6 @@ __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g,
         sig[m] = t % m;
     }
 
-    uint64_t* wbuf = sh.cand + wave * kWaveCandCap;
     // rows unrolled with static register indices (a dynamic index into the
     // prefetched rows would make every load complete before the tile starts)
 #pragma unroll
@@ -622,8 +476,7 @@ __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g,
         if (rr >= nr) break;
         const int r = r0 + rr;
         // All LDS reads of the row first (row table and staged source words),
-        // so their latencies overlap; the candidate writes below could
-        // otherwise alias them and serialise every read.
+        // so their latencies overlap.
         const float* rt = rowtab + (trow0 + rr) * RS;
         // plain float reads (merged into 16-byte reads): LDS accesses through
         // aggregate types carry no type-based alias information, and the
@@ -651,15 +504,7 @@ __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g,
         for (int v = 0; v < kV; ++v) acc[v] = Io<TIn>::decode(x[q], v);
 
         auto emit = [&](int k) {
-            if constexpr (MODE == kModeDetect) {
-                const float t = tab[SO + k - 1];
-                // cheap wave test first: the largest of the lane's kV sums
-                // (NaN operands are ignored by max and fail the compare)
-                const float mx = fmaxf(fmaxf(acc[0], acc[1]), fmaxf(acc[2], acc[3]));
-                const uint64_t any = __builtin_amdgcn_ballot_w64(mx > t);
-                if (__builtin_expect(any != 0, 0))
-                    emit_hits<kV, H>(acc, t, r, k, jb, __builtin_popcountll(any), a, sh, ws, wbuf);
-            } else if constexpr (MODE == kModeLse) {
+            if constexpr (MODE == kModeLse) {
                 float xv[kV];
 #pragma unroll
                 for (int v = 0; v < kV; ++v) xv[v] = (FULL || jb + v < N) ? acc[v] : -__builtin_inff();
@@ -834,12 +679,10 @@ __device__ __forceinline__ void run_tiles(const TileArgs& a, int64_t begin, int6
 
 // Row table for every row of the plane, built once per launch by the whole
 // block: entries of row r refer to the staging layout of r's row block.
-template <int H, int MODE>
-__device__ __forceinline__ void build_whole_table(int T, int R, int c, const float* ta, float scale,
-                                                  float* rowtab)
+template <int H>
+__device__ __forceinline__ void build_whole_table(int T, int R, int c, float* rowtab)
 {
     constexpr int RS = row_table_stride(H);
-    constexpr int SO = row_table_thr_offset(H);
     for (int e = threadIdx.x; e < T * RS; e += kThreads) {
         const int r = e / RS, col = e - r * RS;
         float val = 0.0f;
@@ -852,8 +695,6 @@ __device__ __forceinline__ void build_whole_table(int T, int R, int c, const flo
                     off = stage_offset(m) + (src_row_lo<m>(r, c) - src_row_lo<m>(r0, c)) * stage_row_words(m);
             });
             val = __int_as_float(off);
-        } else if (MODE == kModeDetect && col >= SO && col < SO + H) {
-            val = ta[(int64_t)(col - SO) * T + r] * scale;   // storage units (exact)
         }
         rowtab[e] = val;
     }
@@ -861,12 +702,12 @@ __device__ __forceinline__ void build_whole_table(int T, int R, int c, const flo
 
 // The block's (max, sum) pair of every plane: the 64 lanes of a wave are
 // merged with xor shuffles (both partners of a step compute the same pair,
-// fp32 addition being commutative), the waves in order through LDS (the
-// candidate buffers, unused in this mode); thread k writes plane k.
+// fp32 addition being commutative), the waves in order through LDS; thread
+// k writes plane k.
 template <int H>
 __device__ __forceinline__ void lse_block_pairs(const Smem& sh, WaveState<H>& ws, const TileArgs& a)
 {
-    float* buf = reinterpret_cast<float*>(sh.cand);
+    float* buf = sh.pairs;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int k = 0; k < H; ++k) {
@@ -900,118 +741,63 @@ __device__ __forceinline__ void block_chunk(int64_t n, int64_t& t_begin, int64_t
     t_end = t_begin + q + (b < r ? 1 : 0);
 }
 
+// Detection (kModeDetect) walks the rows of bin tiles with every source value
+// in registers instead (hs_rows.h).
+template <int MODE> struct ModeArgs {
+    using T = TileArgs;
+};
+template <> struct ModeArgs<kModeDetect> {
+    using T = WalkArgs;
+};
+
 // Occupancy asked of the compiler: four waves per SIMD (at most 128 VGPRs)
 // where that needs no scratch, otherwise its own choice.
-template <int H> constexpr int fused_min_waves() { return H <= 8 ? 4 : 1; }
-template <int H> constexpr int batched_min_waves() { return H <= 4 ? 4 : 1; }
+template <int H, int MODE>
+constexpr int fused_min_waves() { return MODE == kModeDetect ? rows::min_waves(H, kV) : (H <= 8 ? 4 : 1); }
+template <int H, int MODE>
+constexpr int fused_threads() { return MODE == kModeDetect ? 64 * rows::block_waves(H, kV) : kThreads; }
 
 template <typename TIn, int H, int MODE>
-__global__ __launch_bounds__(kThreads, fused_min_waves<H>()) void k_fused(TileArgs a, int64_t n_tiles)
+__global__ __launch_bounds__((fused_threads<H, MODE>()), (fused_min_waves<H, MODE>())) void k_fused(
+    typename ModeArgs<MODE>::T a, int64_t n_tiles)
 {
     extern __shared__ __align__(16) float lds[];
-    constexpr int EB = sizeof(typename Io<TIn>::T);
-    const Smem sh = carve<H, EB>(lds, a.T, a.R, a.table_whole != 0);
-    WaveState<H> ws;
-    ws.n = 0;
-    if constexpr (MODE == kModeLse) {
-#pragma unroll
-        for (int k = 0; k < H; ++k) {
-            ws.lm[k] = -__builtin_inff();
-            ws.ls[k] = 0.0f;
-        }
-    }
-    if (a.table_whole) build_whole_table<H, MODE>(a.T, a.R, a.c, a.ta, a.scale, sh.rowtab[0]);
-
-    uint32_t voff[dma_slot_regs(H, EB)];
-    dma_offsets<H, EB>(a.ld, voff);
-
-    if (MODE == kModeDetect) set_flush_params(sh, a.out, a.cap, a.counts, H, a.s_bin, a.kmask);
-
-    if (a.sched) {
-        // full tiles from the list of this block's XCD (blocks are dealt to
-        // the eight XCDs in turn), partial tiles in contiguous chunks
-        const int x = blockIdx.x & 7;
-        const int64_t i = blockIdx.x >> 3;
-        const int64_t per = ((int64_t)gridDim.x - x + 7) >> 3;   // blocks on list x
-        const int64_t lo = a.sched[x], len = (int64_t)a.sched[x + 1] - lo;
-        const TileSeq q{a.sched + 9 + lo + i, per, 0, len > i ? (len - i + per - 1) / per : 0};
-        run_full<TIn, H, MODE>(a, q, sh, voff, ws);
-        int64_t p0, p1;
-        block_chunk((a.N % kTileBins) ? a.row_blocks : 0, p0, p1);
-        run_partial<TIn, H, MODE>(a, p0, p1, sh, voff, ws);
+    if constexpr (MODE == kModeDetect) {
+        rows::walk_plan<TIn, H, kV>(a, reinterpret_cast<unsigned char*>(lds));
     } else {
-        int64_t t0, t1;
-        block_chunk(n_tiles, t0, t1);
-        run_tiles<TIn, H, MODE>(a, t0, t1, sh, voff, ws);
-    }
-
-    if constexpr (MODE == kModeDetect) flush_block<H>(sh, ws.n, a.counts, a.out, a.cap, a.s_bin, a.kmask);
-    if constexpr (MODE == kModeLse) lse_block_pairs<H>(sh, ws, a);
-}
-
-// Batched persistent kernel: the grid walks the tiles of every FOP.
-template <typename TIn, int H>
-__global__ __launch_bounds__(kThreads, batched_min_waves<H>()) void k_batched(BatchArgs b)
-{
-    extern __shared__ __align__(16) float lds[];
-    constexpr int EB = sizeof(typename Io<TIn>::T);
-    const Smem sh = carve<H, EB>(lds, b.T, b.R, b.table_whole != 0);
-    WaveState<H> ws;
-    ws.n = 0;
-    constexpr int align_elems = sizeof(typename Io<TIn>::T) == 4 ? 4 : 8;
-
-    int64_t t0, t1;
-    block_chunk(b.tiles_total, t0, t1);
-    if (t0 >= t1) return;
-    if (b.table_whole) build_whole_table<H, kModeDetect>(b.T, b.R, b.c, b.ta, b.scale, sh.rowtab[0]);
-    // FOP holding tile t0 (binary search over the prefix of tile counts)
-    int f;
-    {
-        int lo = 0, hi = b.n_fops - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (b.tile_prefix[mid] <= t0) lo = mid; else hi = mid - 1;
+        constexpr int EB = sizeof(typename Io<TIn>::T);
+        const Smem sh = carve<H, EB>(lds, a.T, a.R, a.table_whole != 0);
+        WaveState<H> ws;
+        if constexpr (MODE == kModeLse) {
+#pragma unroll
+            for (int k = 0; k < H; ++k) {
+                ws.lm[k] = -__builtin_inff();
+                ws.ls[k] = 0.0f;
+            }
         }
-        f = __builtin_amdgcn_readfirstlane(lo);
-    }
-    for (int64_t tf = t0; tf < t1; ++f) {
-        const int64_t fb = b.tile_prefix[f], fe = min(b.tile_prefix[f + 1], t1);
-        TileArgs a;
-        a.fop = b.fops[f];
-        a.ld = b.lds[f];
-        a.N = b.n_chans[f];
-        a.T = b.T;
-        a.c = b.c;
-        a.R = b.R;
-        a.row_blocks = b.row_blocks;
-        a.scale = b.scale;
-        a.inv_scale = b.inv_scale;
-        a.ta = b.ta;
-        a.out = b.out + b.out_offsets[f];
-        a.cap = b.caps[f];
-        a.counts = b.counts + (int64_t)f * (H + 1);
-        a.s_row = b.s_row;
-        a.s_bin = b.s_bin;
-        a.kmask = b.kmask;
-        a.table_whole = b.table_whole;
-        a.hp = nullptr;
-        a.sched = nullptr;
-        constexpr int eb = sizeof(typename Io<TIn>::T);
-        const bool ok = ((reinterpret_cast<uintptr_t>(a.fop) & 15) == 0) &&
-                        (a.ld % align_elems == 0) && a.ld >= a.N &&
-                        (a.ld * stage_rows(2) + kTileBins) * eb < ((int64_t)1 << 32);
-        if (!ok) {
-            if (threadIdx.x == 0 && tf == fb) a.counts[H] = ~0ull;
+        if (a.table_whole) build_whole_table<H>(a.T, a.R, a.c, sh.rowtab[0]);
+
+        uint32_t voff[dma_slot_regs(H, EB)];
+        dma_offsets<H, EB>(a.ld, voff);
+
+        if (a.sched) {
+            // full tiles from the list of this block's XCD (blocks are dealt to
+            // the eight XCDs in turn), partial tiles in contiguous chunks
+            const int x = blockIdx.x & 7;
+            const int64_t i = blockIdx.x >> 3;
+            const int64_t per = ((int64_t)gridDim.x - x + 7) >> 3;   // blocks on list x
+            const int64_t lo = a.sched[x], len = (int64_t)a.sched[x + 1] - lo;
+            const TileSeq q{a.sched + 9 + lo + i, per, 0, len > i ? (len - i + per - 1) / per : 0};
+            run_full<TIn, H, MODE>(a, q, sh, voff, ws);
+            int64_t p0, p1;
+            block_chunk((a.N % kTileBins) ? a.row_blocks : 0, p0, p1);
+            run_partial<TIn, H, MODE>(a, p0, p1, sh, voff, ws);
         } else {
-            uint32_t voff[dma_slot_regs(H, EB)];
-            dma_offsets<H, EB>(a.ld, voff);
-            set_flush_params(sh, a.out, a.cap, a.counts, H, a.s_bin, a.kmask);
-            // tiles of this FOP segment, numbered from the FOP's first tile
-            run_tiles<TIn, H, kModeDetect>(a, tf - fb, fe - fb, sh, voff, ws);
-            flush_block<H>(sh, ws.n, a.counts, a.out, a.cap, a.s_bin, a.kmask);
-            ws.n = 0;
+            int64_t t0, t1;
+            block_chunk(n_tiles, t0, t1);
+            run_tiles<TIn, H, MODE>(a, t0, t1, sh, voff, ws);
         }
-        tf = fe;
+        if constexpr (MODE == kModeLse) lse_block_pairs<H>(sh, ws, a);
     }
 }
 
@@ -1041,22 +827,20 @@ static hipError_t launch_fused_t(int mode, const TileArgs& a, int64_t n_tiles, i
 {
     // a schedule needs a block on each of its eight lists
     TileArgs b = a;
-    if (mode == kModeDetect) {
-        auto k = k_fused<TIn, H, kModeDetect>;
-        (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        const int g = resident_grid(k, lds_bytes, n_tiles, grid);
-        if (g < 8) b.sched = nullptr;
-        hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), lds_bytes, s, b, n_tiles);
-    } else if (mode == kModeSum) {
-        auto k = k_fused<TIn, H, kModeSum>;
-        (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        const int g = resident_grid(k, lds_bytes, n_tiles, grid);
-        if (g < 8) b.sched = nullptr;
-        hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), lds_bytes, s, b, n_tiles);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    if (mode != kModeSum) return hipErrorInvalidValue;
+    auto k = k_fused<TIn, H, kModeSum>;
+    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
+    const int g = resident_grid(k, lds_bytes, n_tiles, grid);
+    if (g < 8) b.sched = nullptr;
+    hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), lds_bytes, s, b, n_tiles);
     return hipGetLastError();
+}
+
+// Detection in 256-bin tiles.
+template <typename TIn, int H>
+static hipError_t launch_tiles_t(const WalkArgs& a, int grid, hipStream_t s)
+{
+    return rows::launch_plan(k_fused<TIn, H, kModeDetect>, H, kV, a, grid, s);
 }
 
 // The statistic's mode (fp32 storage only; its own translation units).
@@ -1075,16 +859,6 @@ static hipError_t launch_stat_t(int mode, const TileArgs& a, int64_t n_tiles, in
     } else {
         return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-template <typename TIn, int H>
-static hipError_t launch_batched_t(const BatchArgs& b, int grid, int lds_bytes, hipStream_t s)
-{
-    auto k = k_batched<TIn, H>;
-    (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-    const int g = resident_grid(k, lds_bytes, b.tiles_total, grid);
-    hipLaunchKernelGGL(k, dim3(g), dim3(kThreads), lds_bytes, s, b);
     return hipGetLastError();
 }
 

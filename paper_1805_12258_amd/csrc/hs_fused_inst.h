@@ -37,14 +37,13 @@ hipError_t HS_NAMED(launch_fused, HS_INST_NAME, HS_INST_GROUP)(int mode, int H, 
     return hipErrorInvalidValue;
 }
 
-hipError_t HS_NAMED(launch_batched, HS_INST_NAME, HS_INST_GROUP)(int H, const BatchArgs& b, int grid,
-                                                                 int lds, hipStream_t s)
+hipError_t HS_NAMED(launch_tiles, HS_INST_NAME, HS_INST_GROUP)(int H, const WalkArgs& b, int grid, hipStream_t s)
 {
     switch (H - 4 * HS_INST_GROUP) {
-    case 1: return launch_batched_t<HS_INST_T, 4 * HS_INST_GROUP + 1>(b, grid, lds, s);
-    case 2: return launch_batched_t<HS_INST_T, 4 * HS_INST_GROUP + 2>(b, grid, lds, s);
-    case 3: return launch_batched_t<HS_INST_T, 4 * HS_INST_GROUP + 3>(b, grid, lds, s);
-    case 4: return launch_batched_t<HS_INST_T, 4 * HS_INST_GROUP + 4>(b, grid, lds, s);
+    case 1: return launch_tiles_t<HS_INST_T, 4 * HS_INST_GROUP + 1>(b, grid, s);
+    case 2: return launch_tiles_t<HS_INST_T, 4 * HS_INST_GROUP + 2>(b, grid, s);
+    case 3: return launch_tiles_t<HS_INST_T, 4 * HS_INST_GROUP + 3>(b, grid, s);
+    case 4: return launch_tiles_t<HS_INST_T, 4 * HS_INST_GROUP + 4>(b, grid, s);
     }
     return hipErrorInvalidValue;
 }

@@ -22,15 +22,14 @@ constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kLanes;
 constexpr int kRowsPerWave = 4;
 constexpr int kMaxTileRows = kWaves * kRowsPerWave;   // 32
-constexpr int kWaveCandCap = 320;        // per-wave LDS candidate buffer (>= kV*64)
 constexpr int kMaxH = 16;
-constexpr int kCntWords = 32;            // block bookkeeping words of the candidate flush
-constexpr int kFlushParamBytes = 48;     // candidate-output parameters kept in LDS
+constexpr int kTailBytes = 20656;        // LDS a block has after its row table (the statistic's pairs)
 
 // Source words a tile needs per row of stretch factor m: the largest number
 // of distinct floor(j/m) over kTileBins consecutive bins starting at a
 // multiple of kTileBins (j0 mod m is then a multiple of gcd(kTileBins, m),
 // which for a power-of-two tile width is the lowest set bit of m).
+static_assert(kTailBytes >= kWaves * kMaxH * 2 * 4, "pairs of every wave and plane");
 static_assert((kTileBins & (kTileBins - 1)) == 0, "tile width must be a power of two");
 __host__ __device__ constexpr int stage_pitch(int m)
 {
@@ -149,12 +148,11 @@ __host__ __device__ constexpr bool table_whole(int T, int H)
 }
 
 // LDS bytes after the two staging buffers: the row table (two per-tile
-// copies unless it covers the whole plane), the per-wave candidate buffers,
-// the per-plane counters of the block and the candidate-output parameters.
+// copies unless it covers the whole plane) and the tail.
 __host__ __device__ constexpr int smem_tail_bytes(int T, int R, int H)
 {
     return (table_whole(T, H) ? T : 2 * R) * row_table_stride(H) * 4 +
-           kWaves * kWaveCandCap * 8 + kCntWords * 4 + kFlushParamBytes;
+           kTailBytes;
 }
 
 __host__ __device__ inline int64_t floordiv(int64_t a, int64_t b)
@@ -186,7 +184,6 @@ struct TileArgs {
     int64_t cap;
     unsigned long long* counts;   // [H+1]
     int32_t s_row, s_bin;
-    uint32_t kmask;               // (1 << s_k) - 1
     int32_t table_whole;          // row table covers all T rows (built once)
     // materialised planes
     float* hp;              // [H][T][N]
@@ -201,27 +198,7 @@ struct TileArgs {
     float lse_c;            // inv_scale * log2(e) / tau
 };
 
-// Arguments of the batched persistent launch.
-struct BatchArgs {
-    const void* const* fops;
-    const int64_t* lds;
-    const int64_t* n_chans;       // device [n_fops]
-    const int64_t* tile_prefix;   // device [n_fops + 1]
-    int64_t tiles_total;
-    int32_t n_fops;
-    int32_t T, c, R, row_blocks;
-    float scale, inv_scale;
-    const float* ta;
-    hs_cand* out;
-    const int64_t* out_offsets;
-    const int64_t* caps;
-    unsigned long long* counts;   // [n_fops][H+1]
-    int32_t s_row, s_bin;
-    uint32_t kmask;
-    int32_t table_whole;
-};
-
-// Arguments of the strip-walk detection kernel (hs_walk_impl.h), for one FOP
+// Arguments of the detection kernels (hs_rows.h), for one FOP
 // (n_fops == 0: fop, ld, N, out, cap, counts) or a batch (n_fops >= 1: the
 // per-FOP device arrays; out, counts are the bases).
 struct WalkArgs {
@@ -235,17 +212,20 @@ struct WalkArgs {
     const int64_t* out_offsets;   // [n_fops] device
     const int64_t* caps;          // [n_fops] device
     int32_t T, c;                 // rows; row r holds template index r - c
-    int32_t band_split;           // bands [0, band_split) and [band_split, T); 0: one band
     float scale, inv_scale;
     const float* ta;              // [H][T] unscaled
     hs_cand* out;
     int64_t cap;
     unsigned long long* counts;   // [H+1] (batch: [n_fops][H+1])
     int32_t s_row, s_bin;
-    const uint32_t* rowmask;      // [T]: bit m set when floor((r-c)/m) changes at row r
-    const uint32_t* ent;          // schedule entries (band << 24) | strip
+    const uint32_t* ent;          // schedule entries: strips of 64 V bins
     const int32_t* seg;           // [n_seg][4]: FOP, first entry, first index, end index
     const uint32_t* xseg;         // [9]: segments of XCD x are [xseg[x], xseg[x+1])
+    int32_t xfirst[8], xcount[8]; // single FOP: first entry and number of each XCD's strips
+    int64_t units_per_list;       // strips of the longest XCD list
+    int32_t pieces;               // runs each half of a strip's rows is cut into (set by the launcher)
+    int32_t lim_rows, lim_bins;   // batch: a FOP whose (ld * lim_rows + lim_bins) elements take
+                                  // 2^32 bytes or more is rejected
 };
 
 enum Mode { kModeDetect = 0, kModeSum = 1, kModeLse = 2 };
@@ -271,8 +251,7 @@ int fused_lds_bytes(int T, int R, int H, int mode, int elem_bytes);
 
 hipError_t launch_fused(int mode, int dtype, int H, const TileArgs& a, int64_t n_tiles,
                         int grid, int lds_bytes, hipStream_t s);
-hipError_t launch_batched(int dtype, int H, const BatchArgs& a, int grid, int lds_bytes,
-                          hipStream_t s);
+hipError_t launch_tiles(int dtype, int H, const WalkArgs& a, int grid, hipStream_t s);
 hipError_t launch_stream_read(const void* src, int64_t bytes, float* sink, int grid, hipStream_t s);
 hipError_t launch_zero_i64(int64_t* p, int64_t n, hipStream_t s);
 
@@ -307,15 +286,13 @@ hipError_t launch_plane_counts(const hs_cand* out, const int64_t* out_offsets, c
                                unsigned long long* counts, int n_lists, int H, int s_bin, uint32_t kmask,
                                hipStream_t s);
 
-// Strip-walk detection (hs_walk_*.hip): whether a plane's thresholds fit
-// the kernel's LDS table (and the plane has rows enough for its pipeline),
-// which bins-per-lane values V it is built for (strips of 64 V bins), the
-// LDS bytes of a block, and the launcher (grid <= 0: resident grid).
+// Strip-walk detection (hs_walk_*.hip): whether a plane takes it (at least
+// two rows, thresholds of at most 16 KB), which bins-per-lane values V it is
+// built for (strips of 64 V bins), and the launcher (grid <= 0: resident
+// grid).
 bool walk_supported(int T, int H);
 bool walk_v_ok(int V);
-int walk_lds_bytes(int T, int H, int dtype, int V);
-constexpr int kWalkDepth = 2;        // rows in flight per wave; every band has at least this many rows
-hipError_t launch_walk(int dtype, int H, int V, const WalkArgs& a, int grid, int lds_bytes, hipStream_t s);
+hipError_t launch_walk(int dtype, int H, int V, const WalkArgs& a, int grid, hipStream_t s);
 
 // Transpose of the plane map and the log-sum-exp statistic (hs_grad.hip).
 int64_t backward_partial_floats(int T, int H, int R, int64_t N);
@@ -354,23 +331,21 @@ struct hs_plan {
     int lds_bytes = 0;
     int64_t tiles_total = 0;
     int persistent_blocks = 0;
-    std::vector<int64_t> tile_prefix;   // batched: tiles before each FOP
 
     std::vector<uint32_t> sched;         // single FOP: full-tile schedule (empty: chunks)
 
-    // Strip-walk detection: unit schedule and row table, host copy laid out
-    // as the device buffer (offsets in bytes), copied once per device.
-    bool walk = false;
+    // Detection units (strip walk, or tile kernel of a single FOP), host copy
+    // laid out as the device buffer (offsets in bytes), copied once per device.
+    bool walk = false;                   // the strip walk detects
     int walk_v = 4;                      // bins per lane (strips of 64 walk_v bins)
-    int band_split = 0;
     std::vector<unsigned char> walk_tab;
-    size_t off_xseg = 0, off_rowmask = 0, off_seg = 0, off_nchan = 0, off_ent = 0;
-    int walk_lds = 0;
+    size_t off_xseg = 0, off_seg = 0, off_nchan = 0, off_ent = 0;
+    int64_t walk_units = 0;              // strips of the longest XCD list
+    int32_t xfirst[8] = {0}, xcount[8] = {0};   // single FOP: each XCD's strips
 
     // Device copies of the batched tables and of the schedule, made at plan
     // creation on the current device or on first use per device.
     mutable std::mutex mu;
-    mutable int64_t* d_tables[64] = {nullptr};
     mutable uint32_t* d_sched[64] = {nullptr};
     mutable unsigned char* d_walk[64] = {nullptr};
 };

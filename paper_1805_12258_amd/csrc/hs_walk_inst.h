@@ -10,14 +10,14 @@
 
 namespace hsk {
 
-hipError_t HS_WNAMED(launch_walk, HS_WALK_NAME, HS_WALK_V, HS_WALK_GROUP)(int H, const WalkArgs& a, int grid, int lds,
+hipError_t HS_WNAMED(launch_walk, HS_WALK_NAME, HS_WALK_V, HS_WALK_GROUP)(int H, const WalkArgs& a, int grid,
                                                                           hipStream_t s)
 {
     switch (H - 4 * HS_WALK_GROUP) {
-    case 1: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 1, HS_WALK_V>(a, grid, lds, s);
-    case 2: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 2, HS_WALK_V>(a, grid, lds, s);
-    case 3: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 3, HS_WALK_V>(a, grid, lds, s);
-    case 4: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 4, HS_WALK_V>(a, grid, lds, s);
+    case 1: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 1, HS_WALK_V>(a, grid, s);
+    case 2: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 2, HS_WALK_V>(a, grid, s);
+    case 3: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 3, HS_WALK_V>(a, grid, s);
+    case 4: return launch_walk_t<HS_WALK_T, 4 * HS_WALK_GROUP + 4, HS_WALK_V>(a, grid, s);
     }
     return hipErrorInvalidValue;
 }
