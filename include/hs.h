@@ -256,9 +256,10 @@ hs_status hs_detect_batched(const hs_plan* plan, const void* const* fops, const 
 
 /* Sort n candidates in place into the canonical order: ascending CL1 word
  * (row, then plane, then bin; CL1 words are unique within one FOP), a stable
- * radix sort on the low 32 bits of each 8-byte entry.  `work` is device
- * scratch of at least hs_sort_workspace_bytes(n) bytes (that query needs the
- * current HIP device; it returns 0 for n <= 1 or when no device answers). */
+ * sort on the low 32 bits of each 8-byte entry.  `work` is device scratch of
+ * at least hs_sort_workspace_bytes(n) bytes (that query needs the current
+ * HIP device; it returns 0 for n <= 1 or when no device answers, and never
+ * less for a longer list). */
 size_t hs_sort_workspace_bytes(int64_t n);
 hs_status hs_sort_candidates(hs_cand* cand, int64_t n, void* work, void* stream);
 
