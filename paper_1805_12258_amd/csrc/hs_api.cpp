@@ -369,7 +369,6 @@ hsk::FracArgs frac_args(const hs_plan* p, const void* fop, int64_t ld)
     a.inv_scale = 1.0f / p->scale;
     a.s_row = p->s_row;
     a.s_bin = p->s_bin;
-    hsk::frac_magic(a);
     return a;
 }
 
@@ -626,10 +625,7 @@ hs_status hs_detect(const hs_plan* p, const void* fop, int64_t ld, const float* 
             a.counts = reinterpret_cast<unsigned long long*>(counts);
             if (launch_detect(p, a, s) != hipSuccess) return HS_ERR_HIP;
         }
-        if (p->mapping != HS_MAP_FRACTIONAL || capacity == 0) return HS_OK;
-        return from_hip(hsk::launch_plane_counts(out, nullptr, nullptr, capacity,
-                                                 reinterpret_cast<unsigned long long*>(counts), 1, p->H,
-                                                 p->s_bin, (1u << p->s_k) - 1u, s));
+        return HS_OK;
     } catch (...) {
         return HS_ERR_HIP;
     }

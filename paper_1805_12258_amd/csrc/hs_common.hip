@@ -29,70 +29,6 @@ __global__ void k_zero_i64(int64_t* p, int64_t n)
         p[e] = 0;
 }
 
-// Per-plane counts of the candidates a detection stored.  The detection
-// kernels reserve list positions with one atomic per flush and count per
-// plane only the entries dropped for lack of capacity; this pass adds a
-// histogram of the plane field over the first min(total, capacity) entries
-// of each list.  Grid (x, lists); a list whose total is ~0 (a FOP the
-// batched detection rejected) is left as it is.  The list is short (a few
-// MB at most) and latency-bound: each thread keeps kPcU loads in flight (48
-// blocks cover 384 K entries in one round), every entry is one LDS atomic on
-// the block's histogram, and each block adds its H counts with one global
-// atomic per plane.
-constexpr int kPcThreads = 1024;
-constexpr int kPcU = 8;
-constexpr int kPcMaxBlocks = 48;
-
-__global__ __launch_bounds__(kPcThreads) void k_plane_counts(const uint64_t* out, const int64_t* out_offsets,
-                                                             const int64_t* caps, int64_t cap1,
-                                                             unsigned long long* counts, int H, int s_bin,
-                                                             uint32_t kmask)
-{
-    __shared__ unsigned int hist[kMaxH];
-    const int f = blockIdx.y;
-    const uint64_t* o = out + (out_offsets ? out_offsets[f] : 0);
-    const int64_t cap = caps ? caps[f] : cap1;
-    unsigned long long* c = counts + (int64_t)f * (H + 1);
-    const unsigned long long tot = c[H];   // the same for the whole block
-    if (tot == ~0ull) return;
-    const int64_t n = (int64_t)tot < cap ? (int64_t)tot : cap;
-    if (threadIdx.x < kMaxH) hist[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * kPcThreads;
-    for (int64_t e0 = blockIdx.x * (int64_t)kPcThreads + threadIdx.x; e0 < n; e0 += stride * kPcU) {
-        // unconditional loads (indexes clamped into the list), so that all
-        // kPcU are in flight together; entries past the end are not counted
-        uint32_t w[kPcU];
-#pragma unroll
-        for (int u = 0; u < kPcU; ++u) {
-            const int64_t e = e0 + u * stride;
-            w[u] = (uint32_t)o[e < n ? e : n - 1];
-        }
-#pragma unroll
-        for (int u = 0; u < kPcU; ++u)
-            if (e0 + u * stride < n) atomicAdd(&hist[(w[u] >> s_bin) & kmask], 1u);
-    }
-    __syncthreads();
-    if (threadIdx.x < H && hist[threadIdx.x]) atomicAdd(&c[threadIdx.x], (unsigned long long)hist[threadIdx.x]);
-}
-
-hipError_t launch_plane_counts(const hs_cand* out, const int64_t* out_offsets, const int64_t* caps, int64_t cap,
-                               unsigned long long* counts, int n_lists, int H, int s_bin, uint32_t kmask,
-                               hipStream_t s)
-{
-    if (n_lists < 1 || n_lists > 65535 || H < 1 || H > kMaxH) return hipErrorInvalidValue;
-    // one list: enough blocks for its capacity, at most kPcMaxBlocks; a
-    // batch: one block per list
-    int64_t bx = 1;
-    if (n_lists == 1) {
-        bx = (cap + (int64_t)kPcThreads * kPcU - 1) / ((int64_t)kPcThreads * kPcU);
-        bx = bx < 1 ? 1 : (bx > kPcMaxBlocks ? kPcMaxBlocks : bx);
-    }
-    hipLaunchKernelGGL(k_plane_counts, dim3((unsigned)bx, (unsigned)n_lists), dim3(kPcThreads), 0, s,
-                       reinterpret_cast<const uint64_t*>(out), out_offsets, caps, cap, counts, H, s_bin, kmask);
-    return hipGetLastError();
-}
-
 int fused_lds_bytes(int T, int R, int H, int mode, int elem_bytes)
 {
     (void)mode;

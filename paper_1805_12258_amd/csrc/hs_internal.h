@@ -275,16 +275,12 @@ struct FracArgs {
     int64_t cap;
     unsigned long long* counts;
     int32_t s_row, s_bin;
-    uint64_t magic[kMaxH + 1];    // ceil(2^32 / k): floor division by k
+    // set by launch_frac: units of the work (strips x pieces of `rows` rows x
+    // chains)
+    int64_t units;
+    int32_t pieces, rows, groups;
 };
-void frac_magic(FracArgs& a);
 hipError_t launch_frac(int dtype, bool detect, const FracArgs& a, hipStream_t s);
-// Per-plane counts of stored candidates (after a detection kernel): lists at
-// out + out_offsets[f] with capacities caps[f] (or one list of capacity `cap`
-// when both are null), counts [n_lists][H+1].
-hipError_t launch_plane_counts(const hs_cand* out, const int64_t* out_offsets, const int64_t* caps, int64_t cap,
-                               unsigned long long* counts, int n_lists, int H, int s_bin, uint32_t kmask,
-                               hipStream_t s);
 
 // Strip-walk detection (hs_walk_*.hip): whether a plane takes it (at least
 // two rows, thresholds of at most 16 KB), which bins-per-lane values V it is
