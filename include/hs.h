@@ -270,7 +270,7 @@ hs_status hs_sort_candidates(hs_cand* cand, int64_t n, void* work, void* stream)
  *                   with floor((r - c)/m) + c = a and floor(j/m) = b of
  *                   G_m(r, j),   G_m = sum_{k >= m} g_k,  c = N_temp / 2,
  * in unscaled units.  `work` is device scratch of
- * hs_backward_workspace_bytes(plan) bytes (per-tile partial sums).
+ * hs_backward_workspace_bytes(plan) bytes (partial sums).
  * Deterministic: no floating-point atomics, so the same input gives bitwise
  * the same output.  Single-FOP plans only. */
 size_t hs_backward_workspace_bytes(const hs_plan* plan);
@@ -291,8 +291,8 @@ hs_status hs_sum_backward(const hs_plan* plan, const float* g, float* dfop, void
  * FOP (unscaled units), g = *gscale (fp64, device; NULL means 1), so that an
  * autograd engine can pass the upstream gradient without a host copy: the
  * weights exp(HP_k / tau - lse[k-1]) taken through the transpose of
- * hs_sum_backward, formed inside its tile pass from the FOP (no weight plane
- * is stored), then the tile partials added in a fixed order
+ * hs_sum_backward, formed inside its first pass from the FOP (no weight plane
+ * is stored), then the partial sums added in a fixed order
  * (deterministic).  `work` must hold hs_lse_workspace_bytes(plan) bytes.
  * Single-FOP plans only. */
 size_t hs_lse_workspace_bytes(const hs_plan* plan);

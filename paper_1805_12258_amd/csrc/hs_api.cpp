@@ -757,7 +757,7 @@ size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t plane_bytes(const hs_plan* p) { return (size_t)p->T * (size_t)p->N * 4; }
 size_t partial_bytes(const hs_plan* p)
 {
-    return (size_t)hsk::backward_partial_floats((int)p->T, p->H, p->tile_rows, p->N) * 4;
+    return (size_t)hsk::backward_partial_floats((int)p->T, p->H, p->N, true) * 4;
 }
 bool tau_ok(float tau) { return tau > 0.0f && tau < INFINITY; }
 }  // namespace
@@ -775,20 +775,20 @@ hs_status hs_sum_backward(const hs_plan* p, const float* g, float* dfop, void* w
     if (partial_bytes(p) > 0 && !work) return HS_ERR_INVALID;
     try {
         return from_hip(hsk::launch_backward(g, dfop, static_cast<float*>(work), (int)p->T, p->N, p->H,
-                                             p->tile_rows, (hipStream_t)stream));
+                                             (hipStream_t)stream));
     } catch (...) {
         return HS_ERR_HIP;
     }
 }
 
-// Workspace of the statistic: the backward's tile partials (tiles of
-// lse_backward_tile_rows() rows) and the fused forward's per-block pairs;
+// Workspace of the statistic: the backward's partial rows and the fused
+// forward's per-block pairs;
 // for 16-bit plans also the H planes the forward materialises, followed by
 // the larger of the partials and the plane reduction's pairs.
 size_t hs_lse_workspace_bytes(const hs_plan* p)
 {
     if (!p || p->n_fops != 0) return 0;
-    const size_t bwd = (size_t)hsk::backward_partial_floats((int)p->T, p->H, hsk::lse_backward_tile_rows(), p->N) * 4;
+    const size_t bwd = (size_t)hsk::backward_partial_floats((int)p->T, p->H, p->N, false) * 4;
     const size_t fused = (size_t)hsk::kLseMaxBlocks * p->H * 2 * sizeof(float);
     if (p->dtype == HS_DTYPE_F32) return std::max(round256(bwd), round256(fused));
     const size_t tail = std::max(bwd, (size_t)hsk::lse_part_bytes(p->H));
@@ -882,7 +882,7 @@ hs_status hs_lse_backward(const hs_plan* p, const void* fop, int64_t ld, const d
     if (p->mapping != HS_MAP_PAPER) return HS_ERR_UNSUPPORTED;
     if (!fop_ok(p, fop, ld, p->N)) return HS_ERR_INVALID;
     try {
-        // the weights are formed inside the transpose's tile pass: no weight
+        // the weights are formed inside the transpose's first pass: no weight
         // plane is written or read back
         return from_hip(hsk::launch_lse_backward_fused(p->dtype, fop, ld, (int)p->T, p->N, p->H, 1.0f / p->scale,
                                                        (double)tau, lse, gscale, dfop, static_cast<float*>(work),

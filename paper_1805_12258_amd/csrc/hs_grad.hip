@@ -6,13 +6,26 @@
 // where src(r, m) = floor((r - c)/m) + c is the source row of Eq. 1.  The
 // preimage of (a, b) under m is an m x m box of plane points (clipped to the
 // plane).  Two deterministic passes, no floating-point atomics:
-//   1. per tile of 32 rows x 256 bins: read g_H .. g_1 once (coalesced), form
-//      the suffix sums in registers, write G_1 to dFOP, and for m >= 2 stage
-//      G_m in LDS and sum each target's box inside the tile (fixed order) into
-//      a per-(m, tile) partial rectangle in the workspace;
-//   2. per dFOP point: add, for m = 2..H in order, the (at most 4) tile
-//      partials that cover it.
-// The same input gives bitwise the same output.
+//   1. a wave walks a piece of a few rows of a strip of 256 bins, four bins a
+//      lane: it takes g_H .. g_1 of a row (read, or formed from the FOP for
+//      the statistic), forms the suffix sums in registers, writes G_1 to dFOP
+//      and adds G_m, m >= 2, to a register sum over the rows of one target
+//      row; when the target row ends (every m rows), the sum over the m bins
+//      of each target goes to a per-(m, piece) partial row in the workspace;
+//   2. per dFOP point: add, for m = 2..H in order, the partials that cover it
+//      (two where its box lies across strips or pieces, at most four above
+//      the smallest pieces).
+// The same input gives bitwise the same output.  No barrier and little LDS:
+// summing down the rows in registers leaves one horizontal sum every m rows
+// (m = 2, 4, 8, 16 by lanes alone).
+//
+// What bounds it.  The plain transpose: memory, 85 x 2^18 at H = 8 reads 713 MB
+// and writes 145 in 175 us (4.9 TB/s).  The statistic's: the vector units, 32
+// exponentials (a quarter of the rate) and 350 other instructions per row of
+// 256 bins: 85 x 2^20 230 us.  The second pass: 20 and 83 us.  Tiles of rows
+// staged in LDS factor by factor, with a barrier each, and one point per
+// thread in the second pass took 325 us (now 194) and 640 us (now 312); at
+// H = 16, 85 x 2^18, 770 and 908 us (now 489 and 287).
 //
 // Log-sum-exp.  lse_k = log sum_{i,j} exp(HP_k(i,j) / tau) per plane, with a
 // running maximum (each term exp(x - M) <= 1) and a fixed two-level
@@ -23,458 +36,497 @@
 
 #include <type_traits>
 
-#include "hs_internal.h"
+#include "hs_rows.h"
 
 namespace hsk {
 
 namespace {
 
-// Pass 1 tiles are kMaxTileRows x kTileBins like the forward's, covered by
-// 8 waves of 4 rows each.
-constexpr int kGWaves = 8;
-constexpr int kGRows = kMaxTileRows / kGWaves;
+using rows::gptr_t;
+using rows::static_for;
+
+constexpr int kGWaves = 4;                         // waves of a block (independent of each other)
 constexpr int kGThreads = kGWaves * kLanes;
 
-__device__ __forceinline__ int src_row(int r, int m, int c)
+struct BwdArgs {
+    const void* src;                 // the FOP, or g [H][T][N]
+    int64_t ld;                      // of the FOP
+    int32_t T, c, N;
+    int32_t shift, row_blocks, n_bt; // pieces of 2^shift rows, strips
+    float* dfop;
+    float* part;
+    int64_t off[kMaxH + 1];          // start of the partial rows of m
+    // the statistic's weights
+    double inv_scale, tau;
+    float c2;
+    const double* lse;
+    const double* gscale;
+};
+
+constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
+
+// Elements that four bins from a multiple of four read for m.
+constexpr int src_span(int m) { return (m - gcd_c(kV, m) + kV - 1) / m + 1; }
+
+// floor(i / m) for i >= -c (exact for any c >= 0).
+template <int m>
+__device__ __forceinline__ int floor_div(int i, int c)
 {
-    return floordiv32(r - c, m) + c;
+    const int over = (c + m - 1) / m;
+    return (int)((uint32_t)(i + over * m) / (uint32_t)m) - over;
 }
 
-// Offset (in floats) of the partial rectangles of stretch factor m.
-__host__ __device__ inline int64_t partial_offset(int m, int row_blocks, int64_t n_bt)
-{
-    int64_t o = 0;
-    for (int k = 2; k < m; ++k)
-        o += (int64_t)row_blocks * stage_rows(k) * n_bt * stage_pitch(k);
-    return o;
-}
+// Rows of partial sums that a piece of R rows has for m: the most distinct
+// floor(i/m) over R consecutive template indices.
+__host__ __device__ constexpr int piece_rows(int R, int m) { return (R + m - 2) / m + 1; }
 
-// Pass 1: one block per tile (rb, bt).
-__global__ __launch_bounds__(kGThreads) void k_bwd_tiles(const float* __restrict__ g, float* __restrict__ dfop,
-                                                         float* __restrict__ part, int T, int N, int H,
-                                                         int R, int row_blocks, int n_bt)
-{
-    __shared__ float tile[kMaxTileRows * kTileBins];
-    const int rb = blockIdx.x / n_bt;
-    const int bt = blockIdx.x - rb * n_bt;
-    const int r0 = rb * R;
-    const int nr = min(R, T - r0);
-    const int j0 = bt * kTileBins;
-    const int nb = min(kTileBins, N - j0);
-    const int c = T / 2;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int64_t plane = (int64_t)T * N;
+// A partial row of m: the targets floor(j/m), each with the part of its box in
+// the strip where it begins, then for every strip the part of a target that
+// began in the strip before (m bins rarely divide 256), so that the targets
+// are contiguous for the second pass; four elements more for its loads.
+__host__ __device__ inline int targets(int m, int N) { return (N + m - 1) / m; }
+__host__ __device__ inline int partial_pitch(int m, int N, int n_bt) { return (targets(m, N) + n_bt + 7) & ~3; }
 
-    float s[kGRows][kV], nx[kGRows][kV];
-#pragma unroll
-    for (int q = 0; q < kGRows; ++q)
-#pragma unroll
-        for (int v = 0; v < kV; ++v) s[q][v] = 0.0f;
+// The planes' gradients of a row as they are stored.
+template <int H>
+struct PlaneSource {
+    const BwdArgs& a;
+    int lane, j0;
+    bool edge;
+    float nx[1];
 
-    // g_m at the thread's points, into nx (0 outside the tile); 16-byte
-    // loads when the tile is full and the rows are 16-byte aligned
-    const bool vec = nb == kTileBins && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(g) & 15) == 0;
-    auto load_plane = [&](int m) {
-#pragma unroll
-        for (int q = 0; q < kGRows; ++q) {
-            const int rr = wave + kGWaves * q;
-            const float* src = g + (int64_t)(m - 1) * plane + (int64_t)(r0 + (rr < nr ? rr : 0)) * N + j0;
-            if (rr < nr && vec) {
-                const float4 t4 = *reinterpret_cast<const float4*>(src + kV * lane);
-                nx[q][0] = t4.x; nx[q][1] = t4.y; nx[q][2] = t4.z; nx[q][3] = t4.w;
-            } else {
+    __device__ __forceinline__ PlaneSource(const BwdArgs& a_, int lane_, int j0_, int) : a(a_), lane(lane_), j0(j0_)
+    {
+        edge = j0 + kTileBins > a.N;
+    }
+    __device__ __forceinline__ float sign() const { return 1.0f; }
+    __device__ __forceinline__ void request(int, uint32_t) {}
+    __device__ __forceinline__ void weights(int r, float (&G)[H][kV])
+    {
+        const int64_t plane = (int64_t)a.T * a.N * 4;
+        gptr_t p = (gptr_t)(uintptr_t)a.src + ((int64_t)r * a.N + j0) * 4;
+        if (edge) {
+            static_for<1, H>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
 #pragma unroll
                 for (int v = 0; v < kV; ++v) {
                     const int jj = kV * lane + v;
-                    nx[q][v] = (rr < nr && jj < nb) ? src[jj] : 0.0f;
+                    G[k - 1][v] = 0.0f;
+                    if (j0 + jj < a.N) {
+                        uint32_t x[1];
+                        rows::load_words<1, 4>(rows::scalar(p) + (uint32_t)(4 * jj), x);
+                        G[k - 1][v] = __uint_as_float(x[0]);
+                    }
                 }
-            }
+                p += plane;
+            });
+        } else {
+            static_for<1, H>([&](auto kc) {
+                constexpr int k = decltype(kc)::value;
+                uint32_t x[4];
+                rows::load_words<4, 4>(rows::scalar(p) + (uint32_t)(16 * lane), x);
+#pragma unroll
+                for (int v = 0; v < kV; ++v) G[k - 1][v] = __uint_as_float(x[v]);
+                p += plane;
+            });
         }
-    };
-    load_plane(H);
-
-    for (int m = H; m >= 1; --m) {
-        // suffix sum G_m = g_m + G_{m+1} at the thread's points (outside the
-        // tile both are 0)
-#pragma unroll
-        for (int q = 0; q < kGRows; ++q)
-#pragma unroll
-            for (int v = 0; v < kV; ++v) s[q][v] = nx[q][v] + s[q][v];
-        // the next plane's loads fly while this factor's boxes are summed
-        if (m > 1) load_plane(m - 1);
-        if (m == 1) {
-#pragma unroll
-            for (int q = 0; q < kGRows; ++q) {
-                const int rr = wave + kGWaves * q;
-                if (rr >= nr) continue;
-                float* dst = dfop + (int64_t)(r0 + rr) * N + j0;
-#pragma unroll
-                for (int v = 0; v < kV; ++v) {
-                    const int jj = kV * lane + v;
-                    if (jj < nb) dst[jj] = s[q][v];
-                }
-            }
-            break;
-        }
-        __syncthreads();               // the previous factor's gathers are done
-#pragma unroll
-        for (int q = 0; q < kGRows; ++q) {
-            const int rr = wave + kGWaves * q;
-#pragma unroll
-            for (int v = 0; v < kV; ++v) tile[rr * kTileBins + kV * lane + v] = s[q][v];
-        }
-        __syncthreads();
-        // every target cell of the tile for factor m: rows src(r0, m) + tr,
-        // bins floor(j0/m) + tc; its box inside this tile, summed row by row
-        const int NR = stage_rows(m), P = stage_pitch(m);
-        const int lo = src_row(r0, m, c);
-        const int blo = j0 / m;
-        float* out = part + partial_offset(m, row_blocks, n_bt) +
-                     (((int64_t)rb * NR) * n_bt + bt) * P;
-        for (int e = threadIdx.x; e < NR * P; e += kGThreads) {
-            const int tr = e / P, tc = e - tr * P;
-            const int a = lo + tr, b = blo + tc;
-            const int ra = max(c + m * (a - c), r0), rz = min(c + m * (a - c) + m - 1, r0 + nr - 1);
-            const int ja = max(m * b, j0), jz = min(m * b + m - 1, j0 + nb - 1);
-            float acc = 0.0f;
-            for (int r = ra; r <= rz; ++r)
-                for (int j = ja; j <= jz; ++j) acc += tile[(r - r0) * kTileBins + (j - j0)];
-            out[(int64_t)tr * n_bt * P + tc] = acc;
-        }
-    }
-}
-
-// Pass 2: dFOP(a, b) += sum over m = 2..H of the partials covering (a, b).
-__global__ __launch_bounds__(256) void k_bwd_reduce(float* __restrict__ dfop, const float* __restrict__ part,
-                                                    int T, int N, int H, int R, int row_blocks, int n_bt)
-{
-    const int c = T / 2;
-    const int64_t total = (int64_t)T * N;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int a = (int)(e / N), b = (int)(e - (int64_t)a * N);
-        float acc = dfop[e];
-        for (int m = 2; m <= H; ++m) {
-            const int first = max(c + m * (a - c), 0), last = min(c + m * (a - c) + m - 1, T - 1);
-            if (first > last || (int64_t)m * b > N - 1) continue;
-            const int jb0 = m * b, jb1 = min(m * b + m - 1, N - 1);
-            const int NR = stage_rows(m), P = stage_pitch(m);
-            const float* pm = part + partial_offset(m, row_blocks, n_bt);
-            float pmsum = 0.0f;
-            for (int rb = first / R; rb <= last / R; ++rb) {
-                const int tr = a - src_row(rb * R, m, c);
-                for (int bt = jb0 / kTileBins; bt <= jb1 / kTileBins; ++bt) {
-                    const int tc = b - (bt * kTileBins) / m;
-                    pmsum += pm[(((int64_t)rb * NR + tr) * n_bt + bt) * P + tc];
-                }
-            }
-            acc += pmsum;
-        }
-        dfop[e] = acc;
-    }
-}
-
-// ---- statistic backward, weights formed in the transpose's tile pass -------
-//
-// dL/dFOP for L = sum_k tau lse_k is the transpose applied to the weights
-// g_k = gscale exp(HP_k / tau - lse_k).  Instead of writing the H weight
-// planes and reading them back, the tile pass forms them: each thread takes
-// one row and four bins of a 16-row x 256-bin tile, sums HP_1..HP_H from the
-// FOP in the order of Eq. 2 (the forward's sums, so the weights are those of
-// the planes the statistic was taken over), turns each into its weight in
-// registers, forms the suffix sums G_m, writes G_1 to dFOP, and for m >= 2
-// sums each target's m x m box inside the tile into the per-(m, tile)
-// partial rectangles that the second pass adds (the same deterministic
-// layout and order as the plain transpose above).
-template <int A, int B, typename F>
-__host__ __device__ inline void static_for(F&& f)
-{
-    if constexpr (A <= B) {
-        f(std::integral_constant<int, A>{});
-        static_for<A + 1, B>(f);
-    }
-}
-
-constexpr int kFR = 16;                     // rows per tile: one wave each
-constexpr int kFThreads = kFR * kLanes;     // 1024
-
-template <typename TIn> struct GIo;
-template <> struct GIo<float> {
-    __device__ static float ld(const void* p, int64_t e) { return static_cast<const float*>(p)[e]; }
-    // four consecutive values at element e (16-byte aligned)
-    __device__ static void ld4(const void* p, int64_t e, float (&x)[4])
-    {
-        const float4 q = *reinterpret_cast<const float4*>(static_cast<const float*>(p) + e);
-        x[0] = q.x;
-        x[1] = q.y;
-        x[2] = q.z;
-        x[3] = q.w;
-    }
-};
-template <> struct GIo<_Float16> {
-    __device__ static float ld(const void* p, int64_t e) { return (float)static_cast<const _Float16*>(p)[e]; }
-    __device__ static void ld4(const void* p, int64_t e, float (&x)[4])
-    {
-        const uint2 q = *reinterpret_cast<const uint2*>(static_cast<const _Float16*>(p) + e);
-        _Float16 h[4];
-        __builtin_memcpy(h, &q, 8);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = (float)h[v];
-    }
-};
-struct bf16_bits {
-    uint16_t b;
-};
-template <> struct GIo<bf16_bits> {
-    __device__ static float ld(const void* p, int64_t e)
-    {
-        return __uint_as_float((uint32_t)static_cast<const uint16_t*>(p)[e] << 16);
-    }
-    __device__ static void ld4(const void* p, int64_t e, float (&x)[4])
-    {
-        const uint2 q = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p) + e);
-        x[0] = __uint_as_float(q.x << 16);
-        x[1] = __uint_as_float(q.x & 0xffff0000u);
-        x[2] = __uint_as_float(q.y << 16);
-        x[3] = __uint_as_float(q.y & 0xffff0000u);
     }
 };
 
-// Rows of partial sums a 16-row tile produces for stretch factor m: the most
-// distinct floor(i/m) over kFR consecutive template indices.
-__host__ __device__ constexpr int fused_rows(int m) { return (kFR + m - 2) / m + 1; }
-__host__ __device__ inline int64_t fused_partial_offset(int m, int row_blocks, int64_t n_bt)
-{
-    int64_t o = 0;
-    for (int k = 2; k < m; ++k) o += (int64_t)row_blocks * fused_rows(k) * n_bt * stage_pitch(k);
-    return o;
-}
-
-// LDS of one tile.  gt: the tile's G_m values, one row per wave, with zero
-// bins on both sides (the first target column starts up to m - 1 bins
-// before the tile, the last one can end up to 23 bins after it for m <= 16)
-// so that the m-bin sums read zeros outside the tile instead of testing
-// bounds.
-// hr: the rows' m-bin sums (pitch stage_pitch(2), the widest), with zero
-// rows above and below for the same reason on the m-row sums: a target row
-// reaches at most m - 1 rows above the tile and 2m - 2 below.
-constexpr int kGPad = kMaxH;                       // zero bins before the tile
-constexpr int kGPadR = 2 * kMaxH;                  // and after it
-constexpr int kGPitch = kGPad + kTileBins + kGPadR;
-constexpr int kHPitch = stage_pitch(2);
-template <int H> constexpr int hr_top() { return H - 1; }
-template <int H> constexpr int hr_rows() { return kFR + 3 * H - 3; }
-
-// The weight g_k = gscale exp(HP_k / tau - lse_k) in base 2 and fp32, with
-// no fp64 operation per point: with L_k = tau lse_k / input_scale (fp64,
-// in storage units) split as L_hi + L_lo (two fp32 values, L_lo below half
-// an ulp of L_hi),
-//     log2 g_k = (HP - L_hi) c - L_lo c + log2|gscale|,  c = log2(e) / (tau scale),
+// The weights g_k = gscale exp(HP_k / tau - lse_k) of a row, from the FOP:
+// HP_1..HP_H in the order of Eq. 2 (the forward's sums, so the weights are
+// those of the planes the statistic was taken over), no weight plane stored.
+// In base 2 and fp32, with no fp64 operation per point: with L_k = tau lse_k /
+// input_scale (fp64, in storage units) split as L_hi + L_lo (two fp32 values,
+// L_lo below half an ulp of L_hi),
+//     log2 |g_k| = (HP - L_hi) c - L_lo c + log2|gscale|,  c = log2(e) / (tau scale),
 // formed as fma(HP - L_hi, c, K_k) with K_k = -L_lo c + log2|gscale| per
 // plane.  HP - L_hi is exact where HP is within a factor two of L_hi (the
 // weights that matter: lse_k is at least max HP_k / tau), and the remaining
-// roundings leave a few fp32 ulps of relative error in the exponent.  A
-// negative gscale flips the sign of the result, zero gives zero weights.
-// Up to eight planes the tile kernel keeps to 64 VGPRs so that two blocks
-// (eight waves per SIMD) share a compute unit and one block's loads overlap
-// the other's arithmetic.
-template <int H> constexpr int bwd_min_waves() { return H <= 8 ? 8 : 4; }
-
+// roundings leave a few fp32 ulps of relative error in the exponent.  The sign
+// of gscale is applied to the sums, zero gives zero weights.
+//
+// A source value m >= 2 is loaded when its row changes (every m rows) and
+// kept: at most two elements per lane, one vector load.
 template <typename TIn, int H>
-__global__ __launch_bounds__(kFThreads, bwd_min_waves<H>()) void k_lse_bwd_tiles(const void* __restrict__ fop, int64_t ld, int T, int N,
-                                                             double inv_scale, double tau, float c2,
-                                                             const double* __restrict__ lse,
-                                                             const double* __restrict__ gscale_p,
-                                                             float* __restrict__ dfop, float* __restrict__ part,
-                                                             int row_blocks, int n_bt)
-{
-    __shared__ __align__(16) float gt[kFR * kGPitch];
-    __shared__ float hr[hr_rows<H>() * kHPitch];
-    __shared__ float lsplit[2 * H];                  // L_hi, K of every plane
-    const int rb = blockIdx.x / n_bt;
-    const int bt = blockIdx.x - rb * n_bt;
-    const int r0 = rb * kFR;
-    const int nr = min(kFR, T - r0);
-    const int j0 = bt * kTileBins;
-    const int nb = min(kTileBins, N - j0);
-    const int c = T / 2;
-    const int lane = threadIdx.x & 63;
-    const int rr = threadIdx.x >> 6;            // row of the tile (the wave)
-    const int r = r0 + rr;
-    const bool row_ok = rr < nr;
-    const bool full = row_ok && nb == kTileBins;
-    const double gsc = gscale_p ? *gscale_p : 1.0;
-    if (threadIdx.x < H) {
-        const double L = tau * lse[threadIdx.x] / inv_scale;
-        const float hi = (float)L;
-        const float lo = (float)(L - (double)hi);
-        lsplit[2 * threadIdx.x] = hi;
-        lsplit[2 * threadIdx.x + 1] = (float)(-(double)lo * (double)c2 + log2(fabs(gsc)));
-    }
-    // zero pads (never written afterwards)
-    for (int e = threadIdx.x; e < kFR * (kGPad + kGPadR); e += kFThreads) {
-        const int row = e / (kGPad + kGPadR), q = e - row * (kGPad + kGPadR);
-        gt[row * kGPitch + (q < kGPad ? q : kTileBins + q)] = 0.0f;
-    }
-    for (int e = threadIdx.x; e < hr_rows<H>() * kHPitch; e += kFThreads) hr[e] = 0.0f;
+struct LseSource {
+    static constexpr int EB = sizeof(TIn);
+    static constexpr int XW = kV * EB / 4;
+    const BwdArgs& a;
+    const int64_t ldb;
+    bool edge, neg;
+    int jl;
+    uint32_t vx, q[H + 1], rem[H + 1];
+    gptr_t xrow, at[H + 1];
+    uint32_t x[XW], raw[H + 1][2];
+    float hi[H], kk[H];
 
-    // weights of every plane at the thread's four points (0 outside the plane)
-    float G[H][kV];
+    __device__ __forceinline__ LseSource(const BwdArgs& a_, int lane, int j0, int r0) : a(a_), ldb(a_.ld * EB)
     {
-        // every source value first (all loads in flight together), then the
-        // sums.  Plane 1: the thread's four values (one 16-byte load in a
-        // full tile).  m >= 2: the four bins j .. j+3 read elements
-        // floor(j/m) and at most one more, so two loads and a select.
-        const int jl = j0 + kV * lane;
-        const int jc = min(jl, N - 1);                 // lanes past the end read a valid element
-        {
-            const int64_t rowe = (int64_t)(row_ok ? r : 0) * ld;
-            if (nb == kTileBins) {
-                GIo<TIn>::ld4(fop, rowe + jl, G[0]);
-            } else {
-#pragma unroll
-                for (int v = 0; v < kV; ++v) G[0][v] = GIo<TIn>::ld(fop, rowe + min(jl + v, N - 1));
-            }
-        }
+        edge = j0 + kTileBins > a.N;
+        jl = j0 + kV * lane;
+        // lanes past the end read a valid element
+        const int last = (a.N - 1) & ~(kV - 1);
+        const uint32_t jc = (uint32_t)(jl < last ? jl : last);
+        vx = jc * EB;
+        xrow = (gptr_t)(uintptr_t)a.src + r0 * ldb;
         static_for<2, H>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            const int sr = row_ok ? floordiv32(r - c, m) + c : 0;
-            const int e0 = jc / m;
-            const int e1 = min(e0 + 1, (N - 1) / m);
-            const float x0 = GIo<TIn>::ld(fop, (int64_t)sr * ld + e0);
-            const float x1 = GIo<TIn>::ld(fop, (int64_t)sr * ld + e1);
-            const int split = m * (e0 + 1) - jc;           // bins v < split read element e0
-#pragma unroll
-            for (int v = 0; v < kV; ++v) G[m - 1][v] = v < split ? x0 : x1;
+            const uint32_t e = jc / (uint32_t)m;
+            q[m] = e * EB;
+            rem[m] = jc - e * (uint32_t)m;
+            at[m] = (gptr_t)(uintptr_t)a.src + (floor_div<m>(r0 - a.c, a.c) + a.c) * ldb;
         });
-        __syncthreads();                               // split exponents and zero pads are in LDS
-        float acc[kV];
+        const double gsc = a.gscale ? *a.gscale : 1.0;
+        neg = gsc < 0.0;
+        // lane k - 1 forms the constants of plane k
+        const int k = lane < H ? lane : H - 1;
+        const double L = a.tau * a.lse[k] / a.inv_scale;
+        const float h = (float)L;
+        const float lo = (float)(L - (double)h);
+        const float c0 = (float)(-(double)lo * (double)a.c2 + log2(fabs(gsc)));
 #pragma unroll
-        for (int k = 1; k <= H; ++k) {
-            const float lhi = lsplit[2 * (k - 1)], kk = lsplit[2 * (k - 1) + 1];
-#pragma unroll
-            for (int v = 0; v < kV; ++v) {
-                acc[v] = k == 1 ? G[0][v] : acc[v] + G[k - 1][v];
-                G[k - 1][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v] - lhi, c2, kk));
-            }
+        for (int i = 0; i < H; ++i) {
+            hi[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h), i));
+            kk[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c0), i));
         }
-        if (!full) {
+    }
+    __device__ __forceinline__ float sign() const { return neg ? -1.0f : 1.0f; }
+    // the values of the next row; m whose source row begins there are in `fl`
+    __device__ __forceinline__ void request(int first, uint32_t fl)
+    {
+        if (!first) xrow += ldb;
+        rows::load_words<XW, XW * 4>(rows::scalar(xrow) + rows::opaque(vx), x);
+        static_for<2, H>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            constexpr int W = src_span(m);
+            if (fl & (1u << m)) {
+                if (!first) at[m] += ldb;
+                rows::load_words<EB == 4 ? W : W - 1, EB>(rows::scalar(at[m]) + rows::opaque(q[m]), raw[m]);
+            }
+        });
+    }
+    __device__ __forceinline__ void weights(int, float (&G)[H][kV])
+    {
+        float acc[kV];
+        static_for<1, H>([&](auto kc) {
+            constexpr int k = decltype(kc)::value, step = gcd_c(kV, k);   // the remainders' step
 #pragma unroll
             for (int v = 0; v < kV; ++v) {
-                const bool ok = row_ok && kV * lane + v < nb;
+                float y;
+                if constexpr (k == 1) {
+                    y = rows::decode<TIn>(x, v);
+                    acc[v] = y;
+                } else {
+                    const int lo = v / k, left = v % k;
+                    y = rows::decode<TIn>(raw[k], lo);
+                    if (left >= step) y = rem[k] >= (uint32_t)(k - left) ? rows::decode<TIn>(raw[k], lo + 1) : y;
+                    acc[v] = acc[v] + y;
+                }
+                G[k - 1][v] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[v] - hi[k - 1], a.c2, kk[k - 1]));
+            }
+        });
+        if (edge) {
+#pragma unroll
+            for (int v = 0; v < kV; ++v) {
+                const bool ok = jl + v < a.N;
 #pragma unroll
                 for (int k = 0; k < H; ++k) G[k][v] = ok ? G[k][v] : 0.0f;
             }
         }
     }
-    // suffix sums G_m = g_m + G_{m+1}, from the last plane down
-#pragma unroll
-    for (int m = H - 1; m >= 1; --m) {
-#pragma unroll
-        for (int v = 0; v < kV; ++v) G[m - 1][v] = G[m - 1][v] + G[m][v];
-    }
-    if (gsc < 0.0) {
-#pragma unroll
-        for (int m = 0; m < H; ++m)
-#pragma unroll
-            for (int v = 0; v < kV; ++v) G[m][v] = -G[m][v];
-    }
-    if (row_ok) {
-        float* dst = dfop + (int64_t)r * N + j0 + kV * lane;
-        if (full && (N & 3) == 0 && (reinterpret_cast<uintptr_t>(dfop) & 15) == 0) {
-            *reinterpret_cast<float4*>(dst) = make_float4(G[0][0], G[0][1], G[0][2], G[0][3]);
-        } else {
-#pragma unroll
-            for (int v = 0; v < kV; ++v)
-                if (kV * lane + v < nb) dst[v] = G[0][v];
-        }
-    }
-    // box sums of G_m, m >= 2, inside the tile: each wave sums its own row
-    // over the m bins of every target column (no barrier: it reads back
-    // what it wrote), then each target's sum over its m rows; the zero pads
-    // stand for everything outside the tile
-    float* const grow = gt + rr * kGPitch + kGPad;
-    static_for<2, H>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        constexpr int NR = fused_rows(m), P = stage_pitch(m);
-        *reinterpret_cast<float4*>(grow + kV * lane) = make_float4(G[m - 1][0], G[m - 1][1], G[m - 1][2], G[m - 1][3]);
+};
+
+// A wave's row in LDS while its bins are summed over the targets: zero bins on
+// both sides (the first target starts up to m - 1 bins before the strip, the
+// last column can end up to 23 bins after it for m <= 16), so that the sums
+// test no bounds.
+constexpr int kGPad = kMaxH;                       // zero bins before the strip
+constexpr int kGPadR = 2 * kMaxH;                  // and after it
+constexpr int kGPitch = kGPad + kTileBins + kGPadR;
+
+typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// x of the lane whose number differs in the bits of `quad` (1 or 2).
+template <int quad>
+__device__ __forceinline__ float other(float x)
+{
+    constexpr int sel = quad == 1 ? 0xB1 : 0x4E;   // lanes 1 0 3 2, or 2 3 0 1
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), sel, 0xf, 0xf, true));
+}
+
+// The sums of S over the bins of each target of the strip, to the strip's
+// place in a partial row.  `end`: bins of the strip before the plane's end;
+// `side` is the offset from out[0] of the place for a first target that begins
+// in the strip before.
+template <int m>
+__device__ __forceinline__ void emit_targets(const float (&S)[kV], float* row, int j0, int end, int side, int lane,
+                                             float* out)
+{
+    if constexpr (m == 2) {
+        if (kV * lane < end) *reinterpret_cast<float2_a4*>(out + 2 * lane) = float2_a4{S[0] + S[1], S[2] + S[3]};
+    } else if constexpr (m == 4 || m == 8 || m == 16) {
+        float t = (S[0] + S[1]) + (S[2] + S[3]);
+        if constexpr (m >= 8) t += other<1>(t);
+        if constexpr (m >= 16) t += other<2>(t);
+        if ((lane & (m / 4 - 1)) == 0 && kV * lane < end) out[lane / (m / 4)] = t;
+    } else {
+        *reinterpret_cast<float4*>(row + kV * lane) = make_float4(S[0], S[1], S[2], S[3]);
         // the wave reads back bins its other lanes wrote: keep the order
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const int jfirst = m * (j0 / m) - j0;          // first target's first bin, in (-m, 0]
-        if (m > 2) __syncthreads();                    // the previous factor's row sums are read
+        const int jf = -(j0 % m);                  // first target's first bin
+        const float* const s0 = row + jf;
 #pragma unroll
-        for (int tc = lane; tc < P + 63 - (P + 63) % 64; tc += 64) {
-            if (tc < P) {
-                const float* src = grow + jfirst + m * tc;
+        for (int t0 = 0; t0 < stage_pitch(m); t0 += 64) {
+            const int tc = t0 + lane;
+            if (jf + m * tc < end) {
+                const float* src = s0 + m * tc;
                 float acc = src[0];
 #pragma unroll
-                for (int dc = 1; dc < m; ++dc) acc += src[dc];
-                hr[(hr_top<H>() + rr) * kHPitch + tc] = acc;
+                for (int d = 1; d < m; ++d) acc += src[d];
+                out[t0 == 0 && tc == 0 && jf < 0 ? side : tc] = acc;
             }
         }
-        __syncthreads();
-        const int rfirst = c + m * (src_row(r0, m, c) - c) - r0;   // first target's first row, in (-m, 0]
-        float* out = part + fused_partial_offset(m, row_blocks, n_bt) + (((int64_t)rb * NR) * n_bt + bt) * P;
-        for (int e = threadIdx.x; e < NR * P; e += kFThreads) {
-            const int tr = e / P, tc = e - tr * P;
-            const float* src = hr + (hr_top<H>() + rfirst + m * tr) * kHPitch + tc;
-            float acc = src[0];
-#pragma unroll
-            for (int dr = 1; dr < m; ++dr) acc += src[dr * kHPitch];
-            out[(int64_t)tr * n_bt * P + tc] = acc;
-        }
-    });
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
 }
 
-// Second pass of the statistic's backward: dFOP(a, b) += the tile partials
-// covering (a, b) for m = 2..H (m and the tile height are compile-time
-// constants).  Only points that some m >= 2 box maps to are touched: bins
-// b <= (N - 1) / 2 of rows whose boxes meet the plane; each thread takes
-// four consecutive bins of one row.
-template <int H, int R>
-__global__ __launch_bounds__(256) void k_bwd_reduce_t(float* __restrict__ dfop, const float* __restrict__ part, int T,
-                                                      int N, int row_blocks, int n_bt)
+template <int H, typename Source>
+__device__ __forceinline__ void bwd_walk(const BwdArgs& a, float* lds)
 {
-    const int c = T / 2;
-    const int half = (N - 1) / 2 + 1;             // bins with an m = 2 box
-    const int nq = (half + 3) / 4;
-    const int64_t total = (int64_t)T * nq;
-    const bool narrow = total < ((int64_t)1 << 31);   // 32-bit index arithmetic (the usual case)
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int a = narrow ? (int)((uint32_t)e / (uint32_t)nq) : (int)(e / nq);
-        const int b0 = (int)(e - (int64_t)a * nq) * 4;
-        float add[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        bool any = false;
+    const int lane = threadIdx.x & 63;
+    const int wave = rows::uni(threadIdx.x >> 6);
+    // an equal run of the units (piece, strip) for each XCD: neighbouring waves
+    // read neighbouring strips of the same rows
+    const int64_t units = (int64_t)a.n_bt * a.row_blocks;
+    const int xcd = blockIdx.x & 7;
+    const int64_t u = units * xcd / 8 + (int64_t)(blockIdx.x >> 3) * kGWaves + wave;
+    if (u >= units * (xcd + 1) / 8) return;
+    const int rb = (int)((uint32_t)u / (uint32_t)a.n_bt);
+    const int bt = (int)((uint32_t)u - (uint32_t)rb * (uint32_t)a.n_bt);
+    const int r0 = rb << a.shift;
+    const int r1 = min(r0 + (1 << a.shift), a.T);
+    const int j0 = bt * kTileBins;
+    const int end = min(a.N - j0, kTileBins);
+    float* const row = lds + wave * kGPitch + kGPad;
+    if (lane < kGPad) row[lane - kGPad] = 0.0f;
+    if (lane < kGPadR) row[kTileBins + lane] = 0.0f;
+
+    // lane l: the m whose target row begins at row r0 + l (bit m)
+    uint32_t begins = 0;
+    float* out[H + 1];
+    static_for<2, H>([&](auto mc) {
+        constexpr int m = decltype(mc)::value;
+        const int i = r0 + lane - a.c;
+        if (i - m * floor_div<m>(i, a.c) == 0) begins |= 1u << m;
+        out[m] = a.part + a.off[m] + (int64_t)rb * piece_rows(1 << a.shift, m) * partial_pitch(m, a.N, a.n_bt) + j0 / m;
+    });
+    constexpr uint32_t kAll = ~0u;
+
+    Source src(a, lane, j0, r0);
+    float V[H + 1][kV];
+    static_for<2, H>([&](auto mc) {
+#pragma unroll
+        for (int v = 0; v < kV; ++v) V[decltype(mc)::value][v] = 0.0f;
+    });
+    const float sgn = src.sign();
+    src.request(1, kAll);
+#pragma unroll 1
+    for (int r = r0; r < r1; ++r) {
+        float G[H][kV];
+        src.weights(r, G);
+        uint32_t fl = (uint32_t)__builtin_amdgcn_readlane((int)begins, (r + 1 - r0) & 63);
+        if (r + 1 < r1) src.request(0, fl);
+        else fl = kAll;
+        // suffix sums G_m = g_m + G_{m+1}, from the last plane down
+#pragma unroll
+        for (int m = H - 1; m >= 1; --m) {
+#pragma unroll
+            for (int v = 0; v < kV; ++v) G[m - 1][v] = G[m - 1][v] + G[m][v];
+        }
+        float* const dst = a.dfop + (int64_t)r * a.N + j0;
+        if (!src.edge) {
+            *reinterpret_cast<float4_a4*>(dst + kV * lane) =
+                float4_a4{sgn * G[0][0], sgn * G[0][1], sgn * G[0][2], sgn * G[0][3]};
+        } else {
+#pragma unroll
+            for (int v = 0; v < kV; ++v)
+                if (j0 + kV * lane + v < a.N) dst[kV * lane + v] = sgn * G[0][v];
+        }
         static_for<2, H>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            constexpr int NR = fused_rows(m), P = stage_pitch(m);
-            const int first = max(c + m * (a - c), 0), last = min(c + m * (a - c) + m - 1, T - 1);
-            if (first > last) return;
-            const float* pm = part + fused_partial_offset(m, row_blocks, n_bt);
-            for (int rb = first / R; rb <= last / R; ++rb) {
-                const int tr = a - src_row(rb * R, m, c);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int b = b0 + v;
-                    if ((int64_t)m * b > N - 1) continue;
-                    const int jb0 = m * b, jb1 = min(m * b + m - 1, N - 1);
-                    for (int bt = jb0 / kTileBins; bt <= jb1 / kTileBins; ++bt) {
-                        const int tc = b - (bt * kTileBins) / m;
-                        add[v] += pm[(((int64_t)rb * NR + tr) * n_bt + bt) * P + tc];
-                        any = true;
+            for (int v = 0; v < kV; ++v) V[m][v] = V[m][v] + G[m - 1][v];
+            if (fl & (1u << m)) {
+#pragma unroll
+                for (int v = 0; v < kV; ++v) V[m][v] = sgn * V[m][v];
+                emit_targets<m>(V[m], row, j0, end, targets(m, a.N) + bt - j0 / m, lane, out[m]);
+                out[m] += partial_pitch(m, a.N, a.n_bt);
+#pragma unroll
+                for (int v = 0; v < kV; ++v) V[m][v] = 0.0f;
+            }
+        });
+    }
+}
+
+constexpr int bwd_occ(int H) { return H <= 8 ? 4 : 2; }
+
+template <int H>
+__global__ __launch_bounds__(kGThreads, bwd_occ(H)) void k_bwd_tiles(BwdArgs a)
+{
+    __shared__ __align__(16) float lds[kGWaves * kGPitch];
+    bwd_walk<H, PlaneSource<H>>(a, lds);
+}
+
+template <typename TIn, int H>
+__global__ __launch_bounds__(kGThreads, bwd_occ(H)) void k_lse_bwd_tiles(BwdArgs a)
+{
+    __shared__ __align__(16) float lds[kGWaves * kGPitch];
+    bwd_walk<H, LseSource<TIn, H>>(a, lds);
+}
+
+// Pass 2: dFOP(a, b) += the partials covering (a, b), m = 2..H.  Rows a0 + y
+// (those that some box meets), four consecutive bins per thread: per m and
+// piece one vector load, and one element where a target of the four lies
+// across two strips (at most one does).  What depends on the row alone is
+// uniform.
+template <int H, int S>
+struct Reduce {
+    static constexpr int R = 1 << S;              // rows of a piece
+    const BwdArgs& a;
+    int ar, b0;
+    float add[4];
+
+    // m = LO..HI, all their loads in flight together
+    template <int LO, int HI>
+    __device__ __forceinline__ void take()
+    {
+        constexpr int n = HI - LO + 1;
+        float x[n][8], y[n][2];
+        int vs[n];
+        static_for<LO, HI>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            float(&xm)[8] = x[m - LO];
+            float(&ym)[2] = y[m - LO];
+#pragma unroll
+            for (int v = 0; v < 8; ++v) xm[v] = 0.0f;
+            ym[0] = ym[1] = 0.0f;
+            vs[m - LO] = 4;
+            const int i0 = a.c + m * (ar - a.c);
+            const int first = max(i0, 0), last = min(i0 + m - 1, a.T - 1);
+            if (first > last) return;
+            const int nb = targets(m, a.N);
+            if (b0 >= nb) return;
+            // the strip of the four targets' last bin, and the one of them
+            // that begins before it
+            uint32_t o = 0;
+            bool across = false;
+            if constexpr (kTileBins % m != 0) {
+                const int s = (m * (b0 + 4) - 1) / kTileBins, B = s * kTileBins;
+                const int t = (int)((uint32_t)B / (uint32_t)m);
+                across = m * b0 < B && t * m != B && B < a.N;
+                vs[m - LO] = across ? t - b0 : 4;
+                o = (uint32_t)(nb + s) * 4;
+            }
+            const int f = first / R, l = last / R;
+            auto at = [&](int rb) {
+                const int tr = ar - a.c - floor_div<m>(rb * R - a.c, a.c);
+                return rows::scalar((gptr_t)(uintptr_t)(a.part + a.off[m] +
+                                                        ((int64_t)rb * piece_rows(R, m) + tr) *
+                                                            partial_pitch(m, a.N, a.n_bt)));
+            };
+            const gptr_t p = at(f);
+            load4(p, xm);
+            if (across) ym[0] = load1(p, o);
+            if (l > f) {
+                const gptr_t q = at(l);
+                load4(q, xm + 4);
+                if (across) ym[1] = load1(q, o);
+                if constexpr (m > R + 1) {                // pieces lower than m
+                    for (int rb = f + 1; rb < l; ++rb) {
+                        const gptr_t z = at(rb);
+                        float w[4];
+                        load4(z, w);
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) xm[v] += w[v];
+                        if (across) ym[0] += load1(z, o);
                     }
                 }
             }
         });
-        if (any) {
-            float* d = dfop + (int64_t)a * N + b0;
+        static_for<LO, HI>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            const float (&xm)[8] = x[m - LO];
+            const float ys = y[m - LO][0] + y[m - LO][1];
+            const int left = targets(m, a.N) - b0;        // the rest is not of this row
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (b0 + v < half) d[v] = d[v] + add[v];
+            for (int v = 0; v < 4; ++v) {
+                float t = rows::opaque(xm[v]) + rows::opaque(xm[4 + v]);
+                if constexpr (kTileBins % m != 0) t += v == vs[m - LO] ? ys : 0.0f;
+                add[v] += v < left ? t : 0.0f;
+            }
+        });
+    }
+    __device__ __forceinline__ void load4(gptr_t p, float* x) const
+    {
+        uint32_t w[4];
+        rows::load_words<4, 4>(p + (uint32_t)b0 * 4, w);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = __uint_as_float(w[v]);
+    }
+    __device__ static __forceinline__ float load1(gptr_t p, uint32_t o)
+    {
+        uint32_t w[1];
+        rows::load_words<1, 4>(p + o, w);
+        return __uint_as_float(w[0]);
+    }
+};
+
+template <int H, int S>
+__global__ __launch_bounds__(256, 4) void k_bwd_reduce(BwdArgs a, int a0, int n_rows)
+{
+    const int half = (a.N - 1) / 2 + 1;           // bins with an m = 2 box
+    const int bl = 4 * (blockIdx.x * 256 + (int)threadIdx.x);
+    if (bl >= half) return;
+    for (int y = blockIdx.y; y < n_rows; y += gridDim.y) {
+        const int b0 = rows::opaque(bl);          // nothing kept of every m from row to row
+        Reduce<H, S> red{a, a0 + y, b0, {0.0f, 0.0f, 0.0f, 0.0f}};
+        float* const d = a.dfop + (int64_t)(a0 + y) * a.N + b0;
+        float4_a4 g = {0.0f, 0.0f, 0.0f, 0.0f};
+        const bool whole = b0 + 4 <= a.N;
+        if (whole) {
+            g = *reinterpret_cast<const float4_a4*>(d);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 3; ++v)
+                if (b0 + v < a.N) g[v] = d[v];
+        }
+        if constexpr (H <= 8) {
+            red.template take<2, H>();
+        } else {
+            // in groups: registers
+            red.template take<2, 6>();
+            asm volatile("" ::: "memory");
+            red.b0 = rows::opaque(b0);
+            red.template take<7, (H < 11 ? H : 11)>();
+            if constexpr (H > 11) {
+                asm volatile("" ::: "memory");
+                red.b0 = rows::opaque(b0);
+                red.template take<12, H>();
+            }
+        }
+        if (whole) {
+            *reinterpret_cast<float4_a4*>(d) =
+                float4_a4{g[0] + red.add[0], g[1] + red.add[1], g[2] + red.add[2], g[3] + red.add[3]};
+        } else {
+#pragma unroll
+            for (int v = 0; v < 3; ++v)
+                if (b0 + v < a.N) d[v] = g[v] + red.add[v];
         }
     }
 }
@@ -598,75 +650,120 @@ int grid_for(int64_t n, int threads, int cap)
 
 }  // namespace
 
-int64_t backward_partial_floats(int T, int H, int R, int64_t N)
+// Rows of a piece (4, 8 or 16) from the plane's size alone: as many as leave
+// enough pieces to even the load.  Tall pieces write fewer partial rows; the
+// waves of the plain transpose stream, and want more of them (128 x 300001 at
+// H = 8: 407 us with 16 rows, 351 with 8; the statistic's 132 and 152;
+// 85 x 2^18: 203 / 196 / 203 us with 16 / 8 / 4 rows and 73 / 73 / 84).
+int backward_shift(int T, int64_t N, bool planes)
 {
-    const int row_blocks = (T + R - 1) / R;
-    const int64_t n_bt = (N + kTileBins - 1) / kTileBins;
-    return partial_offset(H + 1, row_blocks, n_bt);
+    const int64_t n_bt = (N + kTileBins - 1) / kTileBins, least = planes ? 10000 : 8192;
+    int shift = 4;
+    while (shift > 2 && n_bt * ((T + (1 << shift) - 1) >> shift) < least) --shift;
+    return shift;
 }
 
-hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int64_t N, int H, int R,
-                           hipStream_t s)
+int64_t backward_partial_floats(int T, int H, int64_t N, bool planes)
 {
-    const int row_blocks = (T + R - 1) / R;
-    const int n_bt = (int)((N + kTileBins - 1) / kTileBins);
-    const int64_t tiles = (int64_t)row_blocks * n_bt;
-    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_bwd_tiles, dim3((unsigned)tiles), dim3(kGThreads), 0, s, g, dfop, part, T,
-                       (int)N, H, R, row_blocks, n_bt);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bwd_reduce, dim3(grid_for((int64_t)T * N, 256, 65536)), dim3(256), 0, s, dfop,
-                       part, T, (int)N, H, R, row_blocks, n_bt);
+    const int shift = backward_shift(T, N, planes);
+    const int64_t rows = (T + (1 << shift) - 1) >> shift, n_bt = (N + kTileBins - 1) / kTileBins;
+    int64_t o = 0;
+    for (int m = 2; m <= H; ++m) o += rows * piece_rows(1 << shift, m) * partial_pitch(m, (int)N, (int)n_bt);
+    return o;
+}
+
+namespace {
+
+bool bwd_args(BwdArgs& a, bool planes, const void* src, int64_t ld, int T, int64_t N, int H, float* dfop, float* part)
+{
+    a.src = src;
+    a.ld = ld;
+    a.T = T;
+    a.c = T / 2;
+    a.N = (int32_t)N;
+    a.shift = backward_shift(T, N, planes);
+    a.row_blocks = (T + (1 << a.shift) - 1) >> a.shift;
+    a.n_bt = (int32_t)((N + kTileBins - 1) / kTileBins);
+    a.dfop = dfop;
+    a.part = part;
+    int64_t o = 0;
+    for (int m = 2; m <= kMaxH; ++m) {
+        a.off[m] = o;
+        o += (int64_t)a.row_blocks * piece_rows(1 << a.shift, m) * partial_pitch(m, a.N, a.n_bt);
+    }
+    return H >= 1 && H <= kMaxH && (int64_t)a.row_blocks * a.n_bt <= 0x7fffffff;
+}
+
+unsigned bwd_grid(const BwdArgs& a)
+{
+    const int64_t units = (int64_t)a.row_blocks * a.n_bt;
+    return (unsigned)(8 * ((units + 8 * kGWaves - 1) / (8 * kGWaves) + 1));
+}
+
+// f(integral_constant<int, H>) for H = 1..kMaxH.
+template <int HH, typename F>
+void for_planes(int H, F&& f)
+{
+    if constexpr (HH <= kMaxH) {
+        if (HH == H) f(std::integral_constant<int, HH>{});
+        else for_planes<HH + 1>(H, f);
+    }
+}
+
+template <int H>
+hipError_t launch_bwd_reduce(const BwdArgs& a, hipStream_t s)
+{
+    if constexpr (H >= 2) {
+        const int a0 = a.c - (a.c + 1) / 2, a1 = a.c + (a.T - 1 - a.c) / 2;   // rows with an m = 2 box
+        const int n_rows = a1 - a0 + 1, half = (a.N - 1) / 2 + 1;
+        const auto k = a.shift == 2 ? k_bwd_reduce<H, 2> : a.shift == 3 ? k_bwd_reduce<H, 3> : k_bwd_reduce<H, 4>;
+        hipLaunchKernelGGL(k, dim3((half + 1023) / 1024, n_rows < 32768 ? n_rows : 32768), dim3(256), 0, s, a, a0, n_rows);
+    }
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int64_t N, int H, hipStream_t s)
+{
+    BwdArgs a{};
+    if (!bwd_args(a, true, g, 0, T, N, H, dfop, part)) return hipErrorInvalidValue;
+    hipError_t e = hipErrorInvalidValue;
+    for_planes<1>(H, [&](auto hc) {
+        constexpr int HH = decltype(hc)::value;
+        hipLaunchKernelGGL(k_bwd_tiles<HH>, dim3(bwd_grid(a)), dim3(kGThreads), 0, s, a);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = launch_bwd_reduce<HH>(a, s);
+    });
+    return e;
 }
 
 hipError_t launch_lse_backward_fused(int dtype, const void* fop, int64_t ld, int T, int64_t N, int H, float inv_scale,
                                     double tau, const double* lse, const double* gscale, float* dfop, float* part,
                                     hipStream_t s)
 {
-    const int row_blocks = (T + kFR - 1) / kFR;
-    const int n_bt = (int)((N + kTileBins - 1) / kTileBins);
-    const int64_t tiles = (int64_t)row_blocks * n_bt;
-    if (tiles > 0x7fffffff || H < 1 || H > kMaxH) return hipErrorInvalidValue;
-    const dim3 g((unsigned)tiles), b(kFThreads);
-    const float c2 = (float)(1.4426950408889634 * (double)inv_scale / tau);   // log2(e) / (tau scale)
-    bool ok = false;
-    static_for<1, kMaxH>([&](auto hc) {
+    BwdArgs a{};
+    if (!bwd_args(a, false, fop, ld, T, N, H, dfop, part)) return hipErrorInvalidValue;
+    a.inv_scale = (double)inv_scale;
+    a.tau = tau;
+    a.c2 = (float)(1.4426950408889634 * (double)inv_scale / tau);   // log2(e) / (tau scale)
+    a.lse = lse;
+    a.gscale = gscale;
+    hipError_t e = hipErrorInvalidValue;
+    for_planes<1>(H, [&](auto hc) {
         constexpr int HH = decltype(hc)::value;
-        if (HH != H) return;
-        ok = true;
+        const dim3 grid(bwd_grid(a)), block(kGThreads);
         switch (dtype) {
-        case HS_DTYPE_F32:
-            hipLaunchKernelGGL((k_lse_bwd_tiles<float, HH>), g, b, 0, s, fop, ld, T, (int)N, (double)inv_scale, tau, c2, lse,
-                               gscale, dfop, part, row_blocks, n_bt);
-            break;
-        case HS_DTYPE_F16:
-            hipLaunchKernelGGL((k_lse_bwd_tiles<_Float16, HH>), g, b, 0, s, fop, ld, T, (int)N, (double)inv_scale, tau, c2, lse,
-                               gscale, dfop, part, row_blocks, n_bt);
-            break;
-        case HS_DTYPE_BF16:
-            hipLaunchKernelGGL((k_lse_bwd_tiles<bf16_bits, HH>), g, b, 0, s, fop, ld, T, (int)N, (double)inv_scale, tau,
-                               c2, lse, gscale, dfop, part, row_blocks, n_bt);
-            break;
-        default:
-            ok = false;
+        case HS_DTYPE_F32: hipLaunchKernelGGL((k_lse_bwd_tiles<float, HH>), grid, block, 0, s, a); break;
+        case HS_DTYPE_F16: hipLaunchKernelGGL((k_lse_bwd_tiles<_Float16, HH>), grid, block, 0, s, a); break;
+        case HS_DTYPE_BF16: hipLaunchKernelGGL((k_lse_bwd_tiles<bf16_t, HH>), grid, block, 0, s, a); break;
+        default: return;
         }
+        e = hipGetLastError();
+        if (e == hipSuccess) e = launch_bwd_reduce<HH>(a, s);
     });
-    if (!ok) return hipErrorInvalidValue;
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t quads = (int64_t)T * (((N - 1) / 2 + 1 + 3) / 4);
-    static_for<2, kMaxH>([&](auto hc) {
-        constexpr int HH = decltype(hc)::value;
-        if (HH == H)
-            hipLaunchKernelGGL((k_bwd_reduce_t<HH, kFR>), dim3(grid_for(quads, 256, 65536)), dim3(256), 0, s, dfop,
-                               part, T, (int)N, row_blocks, n_bt);
-    });
-    return hipGetLastError();
+    return e;
 }
-
-int lse_backward_tile_rows() { return kFR; }
 
 int64_t lse_part_bytes(int H) { return (int64_t)H * kLseBlocks * (8 + 4); }
 

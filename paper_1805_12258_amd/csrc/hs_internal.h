@@ -291,16 +291,14 @@ bool walk_v_ok(int V);
 hipError_t launch_walk(int dtype, int H, int V, const WalkArgs& a, int grid, hipStream_t s);
 
 // Transpose of the plane map and the log-sum-exp statistic (hs_grad.hip).
-int64_t backward_partial_floats(int T, int H, int R, int64_t N);
-// The statistic's backward with the weights formed in the transpose's tile
-// pass (tiles of lse_backward_tile_rows() rows; `part` holds
-// backward_partial_floats(T, H, that, N) floats).
+// `part` holds backward_partial_floats(T, H, N, planes) floats (planes: of
+// launch_backward, else of the statistic's).
+int64_t backward_partial_floats(int T, int H, int64_t N, bool planes);
+// The statistic's backward, its weights formed in the transpose's first pass.
 hipError_t launch_lse_backward_fused(int dtype, const void* fop, int64_t ld, int T, int64_t N, int H, float inv_scale,
                                     double tau, const double* lse, const double* gscale, float* dfop, float* part,
                                     hipStream_t s);
-int lse_backward_tile_rows();
-hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int64_t N, int H, int R,
-                           hipStream_t s);
+hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int64_t N, int H, hipStream_t s);
 int64_t lse_part_bytes(int H);
 hipError_t launch_lse_reduce(const float* hp, int64_t plane, int H, double tau, void* work, double* lse,
                              hipStream_t s);
