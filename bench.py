@@ -19,8 +19,7 @@ Prints one JSON line.  `value` is FOP points per second (every point taken
 through all 8 planes and the threshold test).  `roofline` refers to the
 detection kernel the chosen plan launches: algorithmic bytes (one read of
 the FOP + 8 bytes per candidate + the counters) over the average duration
-of one hs_detect call (the counter clear, the detection kernel and the
-per-plane counting pass), measured with HIP events on the launch stream.
+of one hs_detect call (the counter clear and the detection kernel), measured with HIP events on the launch stream.
 `cold_start` times the process's first 60 launches.  `traffic` comes from
 rocprofv3 FETCH_SIZE / WRITE_SIZE counters recorded in profiles/ for that
 kernel and its current sources (null otherwise).  `read_ceiling` times one
@@ -54,19 +53,19 @@ def log(msg):
 
 def detection_kernel(plan, dtype="f32"):
     """Name of the detection kernel the plan launches and the sources it is
-    built from (the tile kernel, the strip walk at V bins per lane or the
-    fractional-mapping kernel)."""
+    built from (the row walk by the tile or the strip kernel, the latter at V
+    bins per lane, or the fractional-mapping kernel)."""
     info, H = plan.info, plan.n_hp
     g = (H - 1) // 4
     if info["detector"] == 1:
         v = info["bins_per_lane"]
         return ("k_walk<%s,%d,%d>" % (CTYPE[dtype], H, v),
-                [CSRC + "hs_walk_impl.h", CSRC + "hs_walk_inst.h",
+                [CSRC + "hs_rows.h", CSRC + "hs_walk_impl.h", CSRC + "hs_walk_inst.h",
                  CSRC + "hs_walk_%s_v%d_g%d.hip" % (dtype, v, g), CSRC + "hs_internal.h"])
     if info["detector"] == 2:
-        return ("k_frac<%s,detect>" % CTYPE[dtype], [CSRC + "hs_frac.hip", CSRC + "hs_internal.h"])
+        return ("k_frac<%s,detect>" % CTYPE[dtype], [CSRC + "hs_frac.hip", CSRC + "hs_rows.h", CSRC + "hs_internal.h"])
     return ("k_fused<%s,%d,detect>" % (CTYPE[dtype], H),
-            [CSRC + "hs_fused_impl.h", CSRC + "hs_fused_inst.h",
+            [CSRC + "hs_rows.h", CSRC + "hs_fused_impl.h", CSRC + "hs_fused_inst.h",
              CSRC + "hs_fused_%s_g%d.hip" % (dtype, g), CSRC + "hs_internal.h"])
 
 
@@ -692,7 +691,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": kname, "launch_ms": r["launch_ms"],
-                     "launch": "one hs_detect call: k_zero_i64 + %s + k_plane_counts" % kname,
+                     "launch": "one hs_detect call: k_zero_i64 + %s" % kname,
                      "algorithmic_bytes": alg_bytes, "fetch_over_ideal": fetch_ideal},
         "seeds": {"ska": synth.SKA["seed"], "batched": synth.BATCHED["seed"],
                   "precision": synth.PRECISION["seed"], "differentiation": synth.DIFF["seed"]},

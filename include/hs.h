@@ -92,7 +92,8 @@ typedef struct hs_plan_desc {
                                /* 0 means 1; must be 1 for HS_DTYPE_F32          */
     int32_t n_fops;            /* 0: single FOP; >= 1: batch of n_fops FOPs      */
     const int64_t* n_chans;    /* HOST array [n_fops]: bins of each FOP          */
-    int32_t tile_rows;         /* tuning: rows per tile, 0 = planner's choice    */
+    int32_t tile_rows;         /* tuning: rows per tile of hs_sum and of the     */
+                               /* statistic, 0 = planner's choice                */
     int32_t persistent_blocks; /* tuning: batched grid size, 0 = planner         */
     int32_t schedule;          /* tuning: which detection kernel and order.      */
                                /* 0 = planner's choice: the strip walk for       */
@@ -154,8 +155,8 @@ hs_status hs_plan_info_get(const hs_plan* plan, hs_plan_info* info);
  * (0: the plan walks tiles in contiguous chunks), or -1 for a NULL plan. */
 int64_t hs_plan_schedule(const hs_plan* plan, uint32_t* words, int64_t capacity);
 
-/* Copy the plan's device tables (unit schedule and row table of the strip
- * walk, tile schedule of the tile kernels, per-FOP table of a batched plan)
+/* Copy the plan's device tables (strip lists of the detection, tile schedule
+ * of the tile kernels, per-FOP table of a batched plan)
  * to the current device, synchronously.  Every GPU call of a plan makes this
  * copy itself on first use on a device, except under stream capture: a call
  * being captured on a device that has no copy yet returns HS_ERR_INVALID and

@@ -6,8 +6,8 @@ tuning only changes speed.  Searched, after the planner's defaults:
 
 * the strip-walk detection kernel with V = 2, 4 or 8 bins per lane
   (`bins_per_lane`; strips of B = 64 V = 128, 256 or 512 bins);
-* the tile kernel (256-bin tiles, 4 bins per lane) with 32, 24 or 16 rows
-  per tile (`tile_rows`);
+* the detection of the tile kernel (256-bin strips, 4 bins per lane), with 32,
+  24 or 16 rows per tile (`tile_rows`, which `hs_sum` and the statistic use);
 * for each, the resident grid or one block per compute unit
   (`persistent_blocks`), and for single-FOP plans the XCD order or
   increasing order of the units (`schedule`).

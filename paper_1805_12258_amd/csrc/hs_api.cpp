@@ -384,8 +384,6 @@ hsk::TileArgs tile_args(const hs_plan* p, const void* fop, int64_t ld, const Dev
     a.row_blocks = p->row_blocks;
     a.scale = p->scale;
     a.inv_scale = 1.0f / p->scale;
-    a.s_row = p->s_row;
-    a.s_bin = p->s_bin;
     a.table_whole = hsk::table_whole((int)p->T, p->H) ? 1 : 0;
     a.sched = t.sched;
     return a;

@@ -1,5 +1,5 @@
 // Dtype-independent parts of the fused kernels: LDS sizing, dispatch on the
-// storage type, the counter-clearing kernel and the per-plane counting pass.
+// storage type, and the counter-clearing kernel.
 #include <hip/hip_runtime.h>
 
 #include "hs_internal.h"

@@ -1,16 +1,15 @@
 // Fused harmonic-summing kernels for gfx950: harmonic planes (Eq. 1-2 of
-// arXiv:1805.12258, Sec. III) with threshold detection, or materialised.
+// arXiv:1805.12258, Sec. III) materialised or taken into the log-sum-exp
+// statistic tile by tile, and, by the row walk of hs_rows.h, detected.
 //
-// Work decomposition (the paper's MultipleHP idea, Sec. IV-C, rebuilt for a
-// GPU): a tile is a block of at most kMaxTileRows template rows x kTileBins
-// consecutive bins.  For each stretch factor m >= 2 the tile reads only the
-// shrunken source range (rows floor(i/m), bins [floor(j0/m),
+// Work decomposition of the tiles (the paper's MultipleHP idea, Sec. IV-C,
+// rebuilt for a GPU): a tile is a block of at most kMaxTileRows template rows
+// x kTileBins consecutive bins.  For each stretch factor m >= 2 the tile reads
+// only the shrunken source range (rows floor(i/m), bins [floor(j0/m),
 // floor((j0+B-1)/m)]); these ranges are staged in LDS once per tile, for fp32
 // straight from global memory with LDS-DMA loads.  Each lane owns kV
 // consecutive bins of one row at a time and keeps the kV partial sums in
-// registers; HP_k is formed for k = 1..H in order (Eq. 2), compared with its
-// row threshold and, in the materialising mode, stored.  No intermediate
-// plane goes to memory in the detection mode.
+// registers; HP_k is formed for k = 1..H in order (Eq. 2).
 //
 // Latency: all loads a wave needs for a tile (its share of the staging and
 // the m = 1 values of all its rows) are issued together, one tile ahead of
@@ -24,13 +23,6 @@
 // the position inside that sub-range of the octave: x, x/2, x/4 and x/8 then
 // fall on one XCD at nearly the same time, and the ranges of m = 2, 4, 8 are
 // L2 hits.  Without a schedule, block b walks a contiguous chunk of tiles.
-//
-// Candidates: each wave appends its hits to a private LDS buffer (ballot +
-// mbcnt, no atomics).  A full buffer is written out with one global atomic
-// per wave that reserves its positions in the list, and the block's last
-// buffers with one atomic for the whole block.  Per-plane counts are formed
-// by a counting pass over the list afterwards (only candidates dropped for
-// lack of capacity are counted here).
 #pragma once
 
 #include <hip/hip_runtime.h>

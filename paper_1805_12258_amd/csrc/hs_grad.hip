@@ -20,12 +20,13 @@
 // (m = 2, 4, 8, 16 by lanes alone).
 //
 // What bounds it.  The plain transpose: memory, 85 x 2^18 at H = 8 reads 713 MB
-// and writes 145 in 175 us (4.9 TB/s).  The statistic's: the vector units, 32
-// exponentials (a quarter of the rate) and 350 other instructions per row of
-// 256 bins: 85 x 2^20 230 us.  The second pass: 20 and 83 us.  Tiles of rows
+// and writes 145 in 211 us of a training step (4.1 TB/s).  The statistic's:
+// the vector units, 32 exponentials (a quarter of the rate) and 350 other
+// instructions per row of 256 bins: 85 x 2^20 230 to 250 us.  The second pass:
+// 20 and 79 us.  Both passes together, repeated, 194 and 312 us; tiles of rows
 // staged in LDS factor by factor, with a barrier each, and one point per
-// thread in the second pass took 325 us (now 194) and 640 us (now 312); at
-// H = 16, 85 x 2^18, 770 and 908 us (now 489 and 287).
+// thread in the second pass took 325 and 640 us (at H = 16, 85 x 2^18, 770 and
+// 908, now 489 and 287).
 //
 // Log-sum-exp.  lse_k = log sum_{i,j} exp(HP_k(i,j) / tau) per plane, with a
 // running maximum (each term exp(x - M) <= 1) and a fixed two-level
@@ -93,7 +94,6 @@ struct PlaneSource {
     const BwdArgs& a;
     int lane, j0;
     bool edge;
-    float nx[1];
 
     __device__ __forceinline__ PlaneSource(const BwdArgs& a_, int lane_, int j0_, int) : a(a_), lane(lane_), j0(j0_)
     {

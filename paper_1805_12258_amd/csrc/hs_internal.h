@@ -178,12 +178,6 @@ struct TileArgs {
     int32_t row_blocks;     // tiles across the rows
     float scale;            // stored = power * scale
     float inv_scale;        // applied when a stored value is converted to fp32
-    const float* ta;        // [H][T], unscaled
-    // detect
-    hs_cand* out;
-    int64_t cap;
-    unsigned long long* counts;   // [H+1]
-    int32_t s_row, s_bin;
     int32_t table_whole;          // row table covers all T rows (built once)
     // materialised planes
     float* hp;              // [H][T][N]
