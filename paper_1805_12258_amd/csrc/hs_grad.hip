@@ -20,13 +20,13 @@
 // (m = 2, 4, 8, 16 by lanes alone).
 //
 // What bounds it.  The plain transpose: memory, 85 x 2^18 at H = 8 reads 713 MB
-// and writes 145 in 211 us of a training step (4.1 TB/s).  The statistic's:
+// and writes 145 in 173 us of a training step (5.0 TB/s).  The statistic's:
 // the vector units, 32 exponentials (a quarter of the rate) and 350 other
 // instructions per row of 256 bins: 85 x 2^20 230 to 250 us.  The second pass:
-// 20 and 79 us.  Both passes together, repeated, 194 and 312 us; tiles of rows
+// 19 and 79 us.  Both passes together, repeated, 168 and 312 us; tiles of rows
 // staged in LDS factor by factor, with a barrier each, and one point per
 // thread in the second pass took 325 and 640 us (at H = 16, 85 x 2^18, 770 and
-// 908, now 489 and 287).
+// 908, now 418 and 287).
 //
 // Log-sum-exp.  lse_k = log sum_{i,j} exp(HP_k(i,j) / tau) per plane, with a
 // running maximum (each term exp(x - M) <= 1) and a fixed two-level
@@ -88,8 +88,11 @@ __host__ __device__ constexpr int piece_rows(int R, int m) { return (R + m - 2) 
 __host__ __device__ inline int targets(int m, int N) { return (N + m - 1) / m; }
 __host__ __device__ inline int partial_pitch(int m, int N, int n_bt) { return (targets(m, N) + n_bt + 7) & ~3; }
 
-// The planes' gradients of a row as they are stored.
-template <int H>
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// The planes' gradients of a row as they are stored.  NT: by loads that leave
+// the caches alone, for planes that are larger than those.
+template <int H, bool NT>
 struct PlaneSource {
     const BwdArgs& a;
     int lane, j0;
@@ -123,10 +126,11 @@ struct PlaneSource {
         } else {
             static_for<1, H>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
-                uint32_t x[4];
-                rows::load_words<4, 4>(rows::scalar(p) + (uint32_t)(16 * lane), x);
+                typedef const __attribute__((address_space(1))) float4_a4* q_t;
+                const q_t at = reinterpret_cast<q_t>(rows::scalar(p) + (uint32_t)(16 * lane));
+                const float4_a4 t = NT ? __builtin_nontemporal_load(at) : *at;
 #pragma unroll
-                for (int v = 0; v < kV; ++v) G[k - 1][v] = __uint_as_float(x[v]);
+                for (int v = 0; v < kV; ++v) G[k - 1][v] = t[v];
                 p += plane;
             });
         }
@@ -246,7 +250,6 @@ constexpr int kGPadR = 2 * kMaxH;                  // and after it
 constexpr int kGPitch = kGPad + kTileBins + kGPadR;
 
 typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
-typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // x of the lane whose number differs in the bits of `quad` (1 or 2).
 template <int quad>
@@ -376,11 +379,11 @@ __device__ __forceinline__ void bwd_walk(const BwdArgs& a, float* lds)
 
 constexpr int bwd_occ(int H) { return H <= 8 ? 4 : 2; }
 
-template <int H>
+template <int H, bool NT>
 __global__ __launch_bounds__(kGThreads, bwd_occ(H)) void k_bwd_tiles(BwdArgs a)
 {
     __shared__ __align__(16) float lds[kGWaves * kGPitch];
-    bwd_walk<H, PlaneSource<H>>(a, lds);
+    bwd_walk<H, PlaneSource<H, NT>>(a, lds);
 }
 
 template <typename TIn, int H>
@@ -728,10 +731,18 @@ hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int6
 {
     BwdArgs a{};
     if (!bwd_args(a, true, g, 0, T, N, H, dfop, part)) return hipErrorInvalidValue;
+    // Planes that the last-level cache (256 MB) cannot hold are read past it:
+    // the tile pass of 85 x 2^18 (713 MB) in a training step 211 -> 173 us, the
+    // step 396 -> 373, planes and transpose of 128 x 2^17 at
+    // H = 12 (805 MB) 450 -> 421; of those that fit it may hold what the
+    // caller has just written (101 x 50000, 162 MB: a step with a product
+    // before it 298 us, 308 read past it).
+    const bool nt = (int64_t)H * T * N * 4 > ((int64_t)256 << 20);
     hipError_t e = hipErrorInvalidValue;
     for_planes<1>(H, [&](auto hc) {
         constexpr int HH = decltype(hc)::value;
-        hipLaunchKernelGGL(k_bwd_tiles<HH>, dim3(bwd_grid(a)), dim3(kGThreads), 0, s, a);
+        const auto k = nt ? k_bwd_tiles<HH, true> : k_bwd_tiles<HH, false>;
+        hipLaunchKernelGGL(k, dim3(bwd_grid(a)), dim3(kGThreads), 0, s, a);
         e = hipGetLastError();
         if (e == hipSuccess) e = launch_bwd_reduce<HH>(a, s);
     });

@@ -222,8 +222,8 @@ __device__ __forceinline__ void fold(uint32_t* v, int lane, int d, Op op)
 // ones]).  Each thread accumulates in registers and the block reduces with
 // wave shuffles: atomics on a handful of LDS words would serialise.  The
 // shuffles were most of the pass (a butterfly per slot, 288 a wave at 16
-// slots: 20.8 us for the 290 K entries of a 16-plane list, 12.1 at 8 planes);
-// folded they are 51 (9.9 and 8.0 us).
+// slots: 20.8 us for a trial's list in a batch at 16 planes, 12.1 at 8 for the
+// 85 x 2^21 plane's); folded they are 51 (9.9 and 8.0 us).
 // HP: plane slots tracked per thread (4, 8 or 16, at least H).
 template <int HP>
 __global__ __launch_bounds__(kST) void k_sel_stats(const uint64_t* __restrict__ cand, int64_t n, KeyCfg cfg,

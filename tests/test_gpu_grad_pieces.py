@@ -21,7 +21,8 @@ from tests.helpers import padded_device
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 3, 2), (2, 257, 3), (5, 1025, 16), (17, 511, 13), (16, 512, 7), (33, 256 * 5 + 1, 9), (85, 256 * 3 + 255, 8),
-          (100, 256 * 130 + 77, 11), (128, 256 * 700 + 1, 6), (3, 256 * 4200 + 255, 5), (21, 256, 1)]
+          (100, 256 * 130 + 77, 11), (128, 256 * 700 + 1, 6), (3, 256 * 4200 + 255, 5), (21, 256, 1),
+          (16, 256 * 2100 + 1, 8)]               # planes larger than the last-level cache
 
 
 @pytest.mark.parametrize("T,N,H", SHAPES)
