@@ -732,11 +732,9 @@ hipError_t launch_backward(const float* g, float* dfop, float* part, int T, int6
     BwdArgs a{};
     if (!bwd_args(a, true, g, 0, T, N, H, dfop, part)) return hipErrorInvalidValue;
     // Planes that the last-level cache (256 MB) cannot hold are read past it:
-    // the tile pass of 85 x 2^18 (713 MB) in a training step 211 -> 173 us, the
-    // step 396 -> 373, planes and transpose of 128 x 2^17 at
-    // H = 12 (805 MB) 450 -> 421; of those that fit it may hold what the
-    // caller has just written (101 x 50000, 162 MB: a step with a product
-    // before it 298 us, 308 read past it).
+    // the tile pass of 85 x 2^18 (713 MB) in a training step 211 -> 173 us; of
+    // planes that fit, it may hold what the caller has just written (101 x
+    // 50000, 162 MB: a step with a product before it 298 us, 308 read past it).
     const bool nt = (int64_t)H * T * N * 4 > ((int64_t)256 << 20);
     hipError_t e = hipErrorInvalidValue;
     for_planes<1>(H, [&](auto hc) {
