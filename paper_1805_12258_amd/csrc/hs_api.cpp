@@ -211,6 +211,25 @@ void build_units(hs_plan* p, bool walk, bool linear)
         nchan = p->n_chans;
     }
     even_runs(on);
+    // Few strips of many rows: lists of whole strips cannot be even (a plane of
+    // 256 bins would be walked by one XCD), so where the longest is more than
+    // an eighth above the mean, and has more pieces of three rows than an XCD
+    // has waves to walk them at once (512 to 768), the waves of all XCDs share
+    // one list.  2^20 x 200 bins 1830 us by one XCD, 270 so; 85 x 1000, whose
+    // pieces all fit, 18 us by lists, 19 by one.
+    int64_t total = 0, longest = 0;
+    for (const auto& l : on) {
+        int64_t n = 0;
+        for (const Run& r : l) n += r.count;
+        total += n;
+        longest = std::max(longest, n);
+    }
+    p->lists = 8 * longest * 8 > 9 * total && longest * p->T > 3 * 512 ? 1 : 8;
+    if (p->lists == 1)
+        for (int x = 1; x < 8; ++x) {
+            on[0].insert(on[0].end(), on[x].begin(), on[x].end());
+            on[x].clear();
+        }
     if (p->n_fops == 0) {
         // one contiguous run of entries per XCD
         std::vector<uint32_t> all;
@@ -338,6 +357,7 @@ hsk::WalkArgs walk_args(const hs_plan* p, const unsigned char* tab)
     a.s_row = p->s_row;
     a.s_bin = p->s_bin;
     a.xseg = reinterpret_cast<const uint32_t*>(tab + p->off_xseg);
+    a.lists = p->lists;
     a.units_per_list = p->walk_units;
     std::memcpy(a.xfirst, p->xfirst, sizeof(a.xfirst));
     std::memcpy(a.xcount, p->xcount, sizeof(a.xcount));

@@ -216,7 +216,8 @@ struct WalkArgs {
     const int32_t* seg;           // [n_seg][4]: FOP, first entry, first index, end index
     const uint32_t* xseg;         // [9]: segments of XCD x are [xseg[x], xseg[x+1])
     int32_t xfirst[8], xcount[8]; // single FOP: first entry and number of each XCD's strips
-    int64_t units_per_list;       // strips of the longest XCD list
+    int32_t lists;                // 8: a list per XCD; 1: one list that all XCDs take from
+    int64_t units_per_list;       // strips of the longest list
     int32_t pieces;               // runs each half of a strip's rows is cut into (set by the launcher)
     int32_t lim_rows, lim_bins;   // batch: a FOP whose (ld * lim_rows + lim_bins) elements take
                                   // 2^32 bytes or more is rejected
@@ -328,7 +329,8 @@ struct hs_plan {
     int walk_v = 4;                      // bins per lane (strips of 64 walk_v bins)
     std::vector<unsigned char> walk_tab;
     size_t off_xseg = 0, off_seg = 0, off_nchan = 0, off_ent = 0;
-    int64_t walk_units = 0;              // strips of the longest XCD list
+    int lists = 8;                       // strip lists: one per XCD, or one for all
+    int64_t walk_units = 0;              // strips of the longest list
     int32_t xfirst[8] = {0}, xcount[8] = {0};   // single FOP: each XCD's strips
 
     // Device copies of the batched tables and of the schedule, made at plan

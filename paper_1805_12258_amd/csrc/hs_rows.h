@@ -557,7 +557,8 @@ struct Walk {
 // floor(i/m) keeps the sign of i), each half into a.pieces runs; the units of
 // a segment of strips are all pieces of the lower halves, then those of the
 // upper ones, so that the source rows in use at one time are those of one
-// half.  The waves on an XCD take its units in turn.
+// half.  The waves on an XCD take its units in turn (all waves those of the one
+// list of a plane of few strips).
 template <typename TIn, int H, int V>
 __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem)
 {
@@ -571,9 +572,10 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
     const int wave = uni(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const bool whole = tab_whole(a.T, H);
-    const int xcd = blockIdx.x & 7;
-    const int nw = (int)((gridDim.x - xcd + 7) >> 3) * W;       // waves on this XCD
-    int64_t at = (int64_t)((int)(blockIdx.x >> 3) * W + wave);
+    const bool shared = a.lists == 1;
+    const int xcd = shared ? 0 : blockIdx.x & 7;
+    const int nw = (int)(shared ? gridDim.x : (gridDim.x - xcd + 7) >> 3) * W;       // waves on this list
+    int64_t at = (int64_t)((int)(shared ? blockIdx.x : blockIdx.x >> 3) * W + wave);
     const int halves = a.c > 0 ? 2 : 1;
     // first strip of a single FOP (its XCD lists are in the arguments),
     // requested before the table is waited for
@@ -702,9 +704,9 @@ static hipError_t launch_plan(void (*k)(WalkArgs, A...), int H, int V, WalkArgs 
     const int lds = lds_bytes(a.T, H, VI);
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (grid <= 0) grid = resident_blocks((const void*)k, 64 * W, lds);
-    if (grid < 8) grid = 8;   // every XCD list needs a block
-    a.pieces = row_pieces(8 * a.units_per_list, a.T, (int64_t)grid * W, tab_whole(a.T, H));
-    const int64_t most = 8 * ((a.units_per_list * (a.T > 1 ? 2 : 1) * a.pieces + W - 1) / W);
+    if (grid < a.lists) grid = a.lists;   // every list needs a block
+    a.pieces = row_pieces(a.lists * a.units_per_list, a.T, (int64_t)grid * W, tab_whole(a.T, H));
+    const int64_t most = a.lists * ((a.units_per_list * (a.T > 1 ? 2 : 1) * a.pieces + W - 1) / W);
     if (grid > most) grid = (int)most;
     hipLaunchKernelGGL(k, dim3(grid), dim3(64 * W), lds, s, a, A{}...);
     return hipGetLastError();
