@@ -218,6 +218,7 @@ struct WalkArgs {
     int32_t xfirst[8], xcount[8]; // single FOP: first entry and number of each XCD's strips
     int32_t lists;                // 8: a list per XCD; 1: one list that all XCDs take from
     int64_t units_per_list;       // strips of the longest list
+    int32_t run;                  // units a wave takes one after another (set by the launcher)
     int32_t pieces;               // runs each half of a strip's rows is cut into (set by the launcher)
     int32_t lim_rows, lim_bins;   // batch: a FOP whose (ld * lim_rows + lim_bins) elements take
                                   // 2^32 bytes or more is rejected
