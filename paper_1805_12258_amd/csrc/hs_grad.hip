@@ -91,48 +91,70 @@ __host__ __device__ inline int partial_pitch(int m, int N, int n_bt) { return (t
 typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // The planes' gradients of a row as they are stored.  NT: by loads that leave
-// the caches alone, for planes that are larger than those.
+// the caches alone, for planes that are larger than those.  In the last strip
+// of a ragged plane the lanes past the end, and the one across it, load the
+// row's last four elements; that one takes its own from them (one load a plane
+// as elsewhere: with a guarded load per bin the pass took 65536 x 100 at H = 16
+// 608 us, 150 so; at H = 8 114 and 43).
 template <int H, bool NT>
 struct PlaneSource {
+    typedef const __attribute__((address_space(1))) float4_a4* q_t;
     const BwdArgs& a;
-    int lane, j0;
+    int j0;
     bool edge;
+    int first;             // bin of the strip that offsets count from (below 0 for a strip of less than four)
+    uint32_t off;
+    int past;              // elements of the lane's load before its own (4 or more: none of them)
 
-    __device__ __forceinline__ PlaneSource(const BwdArgs& a_, int lane_, int j0_, int) : a(a_), lane(lane_), j0(j0_)
+    __device__ __forceinline__ PlaneSource(const BwdArgs& a_, int lane, int j0_, int) : a(a_), j0(j0_)
     {
         edge = j0 + kTileBins > a.N;
+        const int last = edge ? a.N - j0 - kV : kTileBins - kV;
+        first = min(last, 0);
+        const int from = min(kV * lane, last);
+        off = (uint32_t)(from - first) * 4u;
+        past = kV * lane - from;
     }
     __device__ __forceinline__ float sign() const { return 1.0f; }
     __device__ __forceinline__ void request(int, uint32_t) {}
     __device__ __forceinline__ void weights(int r, float (&G)[H][kV])
     {
         const int64_t plane = (int64_t)a.T * a.N * 4;
-        gptr_t p = (gptr_t)(uintptr_t)a.src + ((int64_t)r * a.N + j0) * 4;
-        if (edge) {
+        if (a.N < kV) {        // (rows of less than four elements: one strip)
+            const int lane = threadIdx.x & 63;
+            gptr_t p = (gptr_t)(uintptr_t)a.src + (int64_t)r * a.N * 4;
             static_for<1, H>([&](auto kc) {
                 constexpr int k = decltype(kc)::value;
 #pragma unroll
                 for (int v = 0; v < kV; ++v) {
-                    const int jj = kV * lane + v;
-                    G[k - 1][v] = 0.0f;
-                    if (j0 + jj < a.N) {
-                        uint32_t x[1];
-                        rows::load_words<1, 4>(rows::scalar(p) + (uint32_t)(4 * jj), x);
-                        G[k - 1][v] = __uint_as_float(x[0]);
-                    }
+                    uint32_t x[1];
+                    rows::load_words<1, 4>(rows::scalar(p) + (uint32_t)(4 * min(v, a.N - 1)), x);
+                    G[k - 1][v] = lane == 0 && v < a.N ? __uint_as_float(x[0]) : 0.0f;
                 }
                 p += plane;
             });
-        } else {
-            static_for<1, H>([&](auto kc) {
-                constexpr int k = decltype(kc)::value;
-                typedef const __attribute__((address_space(1))) float4_a4* q_t;
-                const q_t at = reinterpret_cast<q_t>(rows::scalar(p) + (uint32_t)(16 * lane));
-                const float4_a4 t = NT ? __builtin_nontemporal_load(at) : *at;
+            return;
+        }
+        gptr_t p = (gptr_t)(uintptr_t)a.src + ((int64_t)r * a.N + j0 + first) * 4;
+        static_for<1, H>([&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            const q_t at = reinterpret_cast<q_t>(rows::scalar(p) + off);
+            const float4_a4 t = NT ? __builtin_nontemporal_load(at) : *at;
 #pragma unroll
-                for (int v = 0; v < kV; ++v) G[k - 1][v] = t[v];
-                p += plane;
-            });
+            for (int v = 0; v < kV; ++v) G[k - 1][v] = t[v];
+            p += plane;
+        });
+        if (edge) {
+#pragma unroll
+            for (int k = 0; k < H; ++k) {
+#pragma unroll
+                for (int v = 0; v < kV; ++v) {
+                    float y = past == 0 ? G[k][v] : 0.0f;
+#pragma unroll
+                    for (int d = 1; v + d < kV; ++d) y = past == d ? G[k][v + d] : y;
+                    G[k][v] = y;
+                }
+            }
         }
     }
 };
