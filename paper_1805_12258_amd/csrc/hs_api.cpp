@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <new>
 
 #include "hs_internal.h"
@@ -71,6 +72,7 @@ std::vector<std::vector<uint32_t>> walk_strip_lists(int64_t n_strips, int lists,
 {
     std::vector<std::vector<uint32_t>> out(lists);
     if (n_strips < 1) return out;
+    for (auto& l : out) l.reserve((size_t)(n_strips / lists + n_strips / 16 + 2));
     if (linear) {
         // increasing strip order, dealt to the lists in turn
         for (int64_t x = 0; x < n_strips; ++x) out[x % lists].push_back((uint32_t)x);
@@ -99,17 +101,21 @@ std::vector<std::vector<uint32_t>> walk_strip_lists(int64_t n_strips, int lists,
 // then by L (so x/2, x/4, x/8 come just before x), then by row block.
 // Layout: nine list offsets, then the entries (rb << 24) | x.  Empty when
 // the fields do not fit.
-std::vector<uint32_t> build_schedule(int64_t n_full, int row_blocks)
+// `lists` are those of n_full tiles or of one more (walk_strip_lists; the order
+// of the tiles that they share is the same).
+std::vector<uint32_t> build_schedule(const std::vector<std::vector<uint32_t>>& lists, int64_t n_full, int row_blocks)
 {
     std::vector<uint32_t> out;
     if (n_full < 1 || row_blocks < 1 || row_blocks > 255 || n_full >= ((int64_t)1 << 24)) return out;
-    const auto lists = walk_strip_lists(n_full, 8);
     out.reserve(9 + (size_t)n_full * row_blocks);
     out.assign(9, 0);
-    for (int k = 0; k < 8; ++k) out[k + 1] = out[k] + (uint32_t)(lists[k].size() * row_blocks);
-    for (int k = 0; k < 8; ++k)
-        for (uint32_t x : lists[k])
+    for (int k = 0; k < 8; ++k) {
+        for (uint32_t x : lists[k]) {
+            if (x >= n_full) continue;
             for (int rb = 0; rb < row_blocks; ++rb) out.push_back(((uint32_t)rb << 24) | x);
+        }
+        out[k + 1] = (uint32_t)(out.size() - 9);
+    }
     return out;
 }
 
@@ -161,8 +167,10 @@ void even_runs(std::vector<Run> (&on)[8])
 // lists, a batch puts each FOP whole on one XCD (longest first onto the least
 // loaded XCD); the lists are then evened out.
 // Device layout: xseg [9] u32 | seg [n_seg][4] i32 | n_chans [n_fops] i64 |
-// entries u32.
-void build_units(hs_plan* p, bool walk, bool linear)
+// entries u32 | tile schedule u32 (one buffer, so that a plan takes one
+// allocation and one copy).  `tiles`: the lists of the 256-bin tiles of a single
+// FOP, where they are those of the strips.
+void build_units(hs_plan* p, bool walk, bool linear, const std::vector<std::vector<uint32_t>>& tiles)
 {
     const int64_t sb = walk ? 64 * (int64_t)p->walk_v : hsk::kTileBins;
     std::vector<uint32_t> ent;
@@ -174,23 +182,22 @@ void build_units(hs_plan* p, bool walk, bool linear)
     std::vector<Run> on[8];
     std::vector<int64_t> nchan;
     if (p->n_fops == 0) {
-        const auto lists = walk_strip_lists((p->N + sb - 1) / sb, 8, linear);
+        const bool same = !linear && sb == hsk::kTileBins && !tiles.empty();
+        const auto own = same ? std::vector<std::vector<uint32_t>>() : walk_strip_lists((p->N + sb - 1) / sb, 8, linear);
+        const auto& lists = same ? tiles : own;
+        ent.reserve((size_t)((p->N + sb - 1) / sb));
         for (int x = 0; x < 8; ++x) {
             const auto r = add_units(lists[x]);
             if (r.second > 0) on[x].push_back({0, r.first, r.second});
         }
     } else {
-        // one unit list per distinct length
-        std::vector<std::pair<int64_t, std::pair<int64_t, int64_t>>> by_len;   // N -> (first, count)
+        // one unit list per distinct number of strips
+        std::map<int64_t, std::pair<int64_t, int64_t>> by_strips;     // -> (first, count)
         std::vector<std::pair<int64_t, int64_t>> fl(p->n_fops);
         for (int f = 0; f < p->n_fops; ++f) {
-            const int64_t n = p->n_chans[f];
-            auto it = std::find_if(by_len.begin(), by_len.end(), [&](const auto& e) { return e.first == n; });
-            if (it == by_len.end()) {
-                const auto lists = walk_strip_lists((n + sb - 1) / sb, 1, linear);
-                by_len.push_back({n, add_units(lists[0])});
-                it = by_len.end() - 1;
-            }
+            const int64_t n = (p->n_chans[f] + sb - 1) / sb;
+            auto it = by_strips.find(n);
+            if (it == by_strips.end()) it = by_strips.emplace(n, add_units(walk_strip_lists(n, 1, linear)[0])).first;
             fl[f] = it->second;
         }
         // whole FOPs to XCDs: longest first onto the least loaded
@@ -264,11 +271,16 @@ void build_units(hs_plan* p, bool walk, bool linear)
     p->off_seg = align(p->off_xseg + xseg.size() * 4);
     p->off_nchan = align(p->off_seg + seg.size() * 4);
     p->off_ent = align(p->off_nchan + nchan.size() * 8);
-    p->walk_tab.assign(align(p->off_ent + ent.size() * 4), 0);
-    std::memcpy(p->walk_tab.data() + p->off_xseg, xseg.data(), xseg.size() * 4);
-    if (!seg.empty()) std::memcpy(p->walk_tab.data() + p->off_seg, seg.data(), seg.size() * 4);
-    if (!nchan.empty()) std::memcpy(p->walk_tab.data() + p->off_nchan, nchan.data(), nchan.size() * 8);
-    if (!ent.empty()) std::memcpy(p->walk_tab.data() + p->off_ent, ent.data(), ent.size() * 4);
+    p->off_sched = align(p->off_ent + ent.size() * 4);
+    p->tab.assign(p->off_sched + p->sched.size() * 4, 0);
+    auto put = [&](size_t off, const auto& v) {
+        if (!v.empty()) std::memcpy(p->tab.data() + off, v.data(), v.size() * sizeof(v[0]));
+    };
+    put(p->off_xseg, xseg);
+    put(p->off_seg, seg);
+    put(p->off_nchan, nchan);
+    put(p->off_ent, ent);
+    put(p->off_sched, p->sched);
     p->walk = walk;
 }
 
@@ -277,6 +289,14 @@ struct DevTabs {
     const unsigned char* walk = nullptr;   // detection units
     const uint32_t* sched = nullptr;       // full-tile schedule (null: contiguous chunks)
 };
+
+DevTabs tables_at(const hs_plan* p, const unsigned char* tab)
+{
+    DevTabs t;
+    t.walk = tab;
+    if (tab && !p->sched.empty()) t.sched = reinterpret_cast<const uint32_t*>(tab + p->off_sched);
+    return t;
+}
 
 hs_status copy_to_device(const void* src, size_t bytes, void** dst)
 {
@@ -306,26 +326,16 @@ hs_status device_tables(const hs_plan* p, hipStream_t stream, DevTabs* t)
         if (hipStreamGetDevice(stream, &sd) != hipSuccess || (int)sd != dev) return HS_ERR_INVALID;
     }
     std::lock_guard<std::mutex> g(p->mu);
-    const bool need_walk = !p->walk_tab.empty() && !p->d_walk[dev];
-    const bool need_sched = !p->sched.empty() && !p->d_sched[dev];
-    if (need_walk || need_sched) {
+    if (!p->tab.empty() && !p->d_tab[dev]) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &cs) != hipSuccess) return HS_ERR_HIP;
         if (cs != hipStreamCaptureStatusNone) return HS_ERR_INVALID;
         void* d = nullptr;
-        if (need_walk) {
-            const hs_status st = copy_to_device(p->walk_tab.data(), p->walk_tab.size(), &d);
-            if (st != HS_OK) return st;
-            p->d_walk[dev] = static_cast<unsigned char*>(d);
-        }
-        if (need_sched) {
-            const hs_status st = copy_to_device(p->sched.data(), p->sched.size() * sizeof(uint32_t), &d);
-            if (st != HS_OK) return st;
-            p->d_sched[dev] = static_cast<uint32_t*>(d);
-        }
+        const hs_status st = copy_to_device(p->tab.data(), p->tab.size(), &d);
+        if (st != HS_OK) return st;
+        p->d_tab[dev] = static_cast<unsigned char*>(d);
     }
-    t->walk = p->d_walk[dev];
-    t->sched = p->d_sched[dev];
+    *t = tables_at(p, p->d_tab[dev]);
     return HS_OK;
 }
 
@@ -342,8 +352,7 @@ hs_status device_tables_present(const hs_plan* p, hipStream_t stream, DevTabs* t
         if (hipStreamGetDevice(stream, &sd) != hipSuccess || (int)sd != dev) return HS_ERR_INVALID;
     }
     std::lock_guard<std::mutex> g(p->mu);
-    t->walk = p->d_walk[dev];
-    t->sched = p->d_sched[dev];
+    *t = tables_at(p, p->d_tab[dev]);
     return HS_OK;
 }
 
@@ -500,16 +509,19 @@ hs_status hs_plan_create(hs_plan** out, const hs_plan_desc* d)
         const bool paper = d->mapping == HS_MAP_PAPER;   // the fractional mapping has a kernel of its own
         const bool walk = paper && want_walk && hsk::walk_supported((int)p->T, p->H);
 
+        std::vector<std::vector<uint32_t>> tiles;
         if (d->n_fops == 0) {
             p->tiles_total = p->row_blocks * bin_tiles(p->N);
-            if (paper && (d->schedule == 0 || d->schedule == 2 || d->schedule == 4))
-                p->sched = build_schedule(p->N / hsk::kTileBins, p->row_blocks);
+            if (paper && (d->schedule == 0 || d->schedule == 2 || d->schedule == 4)) {
+                tiles = walk_strip_lists(bin_tiles(p->N), 8);
+                p->sched = build_schedule(tiles, p->N / hsk::kTileBins, p->row_blocks);
+            }
         } else {
             int64_t acc = 0;
             for (int64_t n : p->n_chans) acc += p->row_blocks * bin_tiles(n);
             p->tiles_total = acc;
         }
-        if (paper) build_units(p, walk, d->schedule == 1 || d->schedule == 3);
+        if (paper) build_units(p, walk, d->schedule == 1 || d->schedule == 3, tiles);
         *out = p;
         return HS_OK;
     } catch (const std::bad_alloc&) {
@@ -525,10 +537,9 @@ hs_status hs_plan_destroy(hs_plan* p)
     int cur = -1;
     bool have_dev = hipGetDevice(&cur) == hipSuccess;
     for (int dev = 0; dev < 64; ++dev) {
-        if (p->d_sched[dev] || p->d_walk[dev]) {
+        if (p->d_tab[dev]) {
             if (have_dev) (void)hipSetDevice(dev);
-            if (p->d_sched[dev]) (void)hipFree(p->d_sched[dev]);
-            if (p->d_walk[dev]) (void)hipFree(p->d_walk[dev]);
+            (void)hipFree(p->d_tab[dev]);
         }
     }
     if (have_dev && cur >= 0) (void)hipSetDevice(cur);

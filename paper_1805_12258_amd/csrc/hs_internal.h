@@ -324,19 +324,17 @@ struct hs_plan {
 
     std::vector<uint32_t> sched;         // single FOP: full-tile schedule (empty: chunks)
 
-    // Detection units (strip walk, or tile kernel of a single FOP), host copy
-    // laid out as the device buffer (offsets in bytes), copied once per device.
+    // Detection units and the tile schedule, host copy laid out as the device
+    // buffer (offsets in bytes), copied once per device.
     bool walk = false;                   // the strip walk detects
     int walk_v = 4;                      // bins per lane (strips of 64 walk_v bins)
-    std::vector<unsigned char> walk_tab;
-    size_t off_xseg = 0, off_seg = 0, off_nchan = 0, off_ent = 0;
+    std::vector<unsigned char> tab;
+    size_t off_xseg = 0, off_seg = 0, off_nchan = 0, off_ent = 0, off_sched = 0;
     int lists = 8;                       // strip lists: one per XCD, or one for all
     int64_t walk_units = 0;              // strips of the longest list
     int32_t xfirst[8] = {0}, xcount[8] = {0};   // single FOP: each XCD's strips
 
-    // Device copies of the batched tables and of the schedule, made at plan
-    // creation on the current device or on first use per device.
+    // Device copies of `tab`, made on first use per device.
     mutable std::mutex mu;
-    mutable uint32_t* d_sched[64] = {nullptr};
-    mutable unsigned char* d_walk[64] = {nullptr};
+    mutable unsigned char* d_tab[64] = {nullptr};
 };
