@@ -102,3 +102,25 @@ def test_time_does_not_depend_on_the_words(n):
     us = {k: sort_us(k, n) for k in ("spread", "fields", "lowbins", "rednoise", "row", "far", "equal")}
     print("case", n, {k: round(v, 1) for k, v in us.items()}, flush=True)
     assert max(us.values()) <= 4 * us["spread"]
+
+
+@pytest.mark.parametrize("n", [1500, 9000, 60000])
+def test_replays_of_a_captured_sort(n):
+    """The passes of every length in a graph, replayed on new lists with eager
+    work between the replays."""
+    _, a = entries("fields", n)
+    dev = torch.from_numpy(a.copy()).cuda()
+    work = torch.empty(hs.hs_sort_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    hs.hs_sort_candidates(dev, n, work)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hs.hs_sort_candidates(dev, n, work)
+    for kind in ("row", "fields", "few", "spread"):
+        w, a = entries(kind, n)
+        dev.copy_(torch.from_numpy(a.copy()))
+        graph.replay()
+        got = dev.cpu().numpy()
+        assert np.array_equal(got, a[np.argsort(w, kind="stable")]), kind
+        work.random_()
+        torch.cuda.synchronize()
