@@ -85,7 +85,7 @@ __host__ __device__ constexpr int piece_rows(int R, int m) { return (R + m - 2) 
 // the strip where it begins, then for every strip the part of a target that
 // began in the strip before (m bins rarely divide 256), so that the targets
 // are contiguous for the second pass; four elements more for its loads.
-__host__ __device__ inline int targets(int m, int N) { return (N + m - 1) / m; }
+__host__ __device__ inline int targets(int m, int N) { return (N - 1) / m + 1; }
 __host__ __device__ inline int partial_pitch(int m, int N, int n_bt) { return (targets(m, N) + n_bt + 7) & ~3; }
 
 typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
