@@ -95,17 +95,18 @@ typedef struct hs_plan_desc {
     int32_t tile_rows;         /* tuning: rows per tile of hs_sum and of the     */
                                /* statistic, 0 = planner's choice                */
     int32_t persistent_blocks; /* tuning: batched grid size, 0 = planner         */
-    int32_t schedule;          /* tuning: which detection kernel and order.      */
-                               /* 0 = planner's choice: the strip walk for       */
-                               /* 16-bit storage or more than 8 planes, the tile */
-                               /* kernel otherwise; 4 = strip walk; 2 = tile     */
-                               /* kernel (walk units and tiles dealt to the      */
-                               /* eight XCDs so that sources are L2 hits);       */
-                               /* 1 = strip walk, 3 = tile kernel, both in       */
-                               /* increasing order (contiguous chunks).  The     */
-                               /* walk needs N_temp >= 2 and a threshold table   */
-                               /* of at most 16 KB; otherwise the tile kernel    */
-                               /* runs.  Results do not depend on it.            */
+    int32_t schedule;          /* tuning: width and order of the detection's     */
+                               /* strips.  4 = strip walk (64 V bins, V =        */
+                               /* bins_per_lane), 2 = tile kernel (256 bins; the */
+                               /* same walk), both with strips dealt to the      */
+                               /* eight XCDs so that sources are L2 hits; 1 =    */
+                               /* strip walk, 3 = tile kernel, strips (and tiles */
+                               /* of the other calls) in increasing order.  0 =  */
+                               /* planner's choice: 4 for 16-bit storage or more */
+                               /* than 8 planes, else 2.  The strip walk needs   */
+                               /* N_temp >= 2 and a threshold table of at most   */
+                               /* 16 KB; otherwise the tile kernel runs.         */
+                               /* Results do not depend on it.                   */
     int32_t mapping;           /* hs_mapping (0 = HS_MAP_PAPER)                  */
     int32_t bins_per_lane;     /* tuning: bins per lane V of the strip walk (2,  */
                                /* 4 or 8: strips of 64 V bins); 0 = planner (8  */

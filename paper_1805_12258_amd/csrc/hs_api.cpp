@@ -420,13 +420,6 @@ hsk::TileArgs tile_args(const hs_plan* p, const void* fop, int64_t ld, const Dev
 
 int64_t bin_tiles(int64_t n) { return (n + hsk::kTileBins - 1) / hsk::kTileBins; }
 
-// Persistent grid override (0: the launcher sizes the grid from occupancy).
-int persistent_grid(const hs_plan* p, int64_t tiles)
-{
-    (void)tiles;
-    return p->persistent_blocks;
-}
-
 }  // namespace
 
 extern "C" {
@@ -454,9 +447,14 @@ hs_status hs_plan_create(hs_plan** out, const hs_plan_desc* d)
         hs_plan* p = new hs_plan();
         p->mapping = d->mapping;
         // bins per lane of the strip walk: eight for 16-bit storage up to
-        // eight planes (the rings of 512-bin strips still leave four waves
-        // per SIMD) and for batches (measured faster at H = 16, fp32), else
-        // four
+        // eight planes and for batches, else four.  us a call at 8 / 4 / 2:
+        // 85 x 2^21 fp16, eight planes 131 / 141 / 254, four planes 85 / 109 /
+        // 189; bf16 85 x 2^20 71 / 81 / 122; six FOPs of 85 x 2^20, fp32 at 16
+        // planes 720 / 736 / 1164, fp16 at eight 358 / 439 / 753.  Where four is
+        // the choice the two are alike (fp32 174 / 176; 16 planes, where a
+        // strip of eight is walked as two halves, 249 / 253 fp32 and 247 / 247
+        // fp16; 85 x 2^18 at 16 planes 53 / 47); small planes want more strips
+        // (21 x 2^16 fp16 14.1 / 12.5)
         p->walk_v = d->bins_per_lane ? d->bins_per_lane
                                      : ((d->dtype != HS_DTYPE_F32 && d->n_hp <= 8) || d->n_fops > 0 ? 8 : 4);
         p->T = d->n_temp;
@@ -496,14 +494,14 @@ hs_status hs_plan_create(hs_plan** out, const hs_plan_desc* d)
         p->row_blocks = (int)((p->T + R - 1) / R);
         p->lds_bytes = hsk::fused_lds_bytes((int)p->T, R, p->H, hsk::kModeDetect, elem_bytes(p->dtype));
 
-        // detection: the strip walk (XCD lists by octave position; increasing
-        // strip order for schedule 1) where its threshold table fits and it
-        // is the faster kernel, else the tile kernel.  Measured on 85 x 2^21
-        // planes, the walk wins with 16-bit storage and with more than eight
-        // planes, the tile kernel with fp32 storage up to eight: schedule 0
-        // picks by that rule, 1 and 4 ask for the walk, 2 and 3 for the tile
-        // kernel.  The tile kernels of the other calls use the XCD tile
-        // schedule for 0, 2 and 4, contiguous chunks for 1 and 3.
+        // detection: one walk over rows (hs_rows.h) under two names.  The strip
+        // walk takes walk_v bins per lane, the tile kernel four: the same
+        // kernel where walk_v is four (fp32 85 x 2^21 176 us by either name),
+        // so the choice matters for the 16-bit planes and batches above.
+        // schedule 1 and 4 ask for the strip walk, 2 and 3 for the tile kernel;
+        // 0 and 4, 2 deal strips to XCDs by octave position, 1 and 3 in
+        // increasing order.  The tile kernels of the other calls use the XCD
+        // tile schedule for 0, 2 and 4, contiguous chunks for 1 and 3.
         const bool walk_wins = p->dtype != HS_DTYPE_F32 || p->H > 8;
         const bool want_walk = d->schedule == 1 || d->schedule == 4 || (d->schedule == 0 && walk_wins);
         const bool paper = d->mapping == HS_MAP_PAPER;   // the fractional mapping has a kernel of its own
@@ -615,7 +613,7 @@ hs_status hs_sum(const hs_plan* p, const void* fop, int64_t ld, float* hp, void*
         hsk::TileArgs a = tile_args(p, fop, ld, t);
         a.hp = hp;
         return from_hip(hsk::launch_fused(hsk::kModeSum, p->dtype, p->H, a, p->tiles_total,
-                                          persistent_grid(p, p->tiles_total), p->lds_bytes,
+                                          p->persistent_blocks, p->lds_bytes,
                                           (hipStream_t)stream));
     } catch (...) {
         return HS_ERR_HIP;
@@ -894,7 +892,7 @@ hs_status hs_lse_forward(const hs_plan* p, const void* fop, int64_t ld, float ta
         hsk::TileArgs a = tile_args(p, fop, ld, t);
         a.hp = planes;
         hipError_t e = hsk::launch_fused(hsk::kModeSum, p->dtype, p->H, a, p->tiles_total,
-                                         persistent_grid(p, p->tiles_total), p->lds_bytes, s);
+                                         p->persistent_blocks, p->lds_bytes, s);
         if (e != hipSuccess) return HS_ERR_HIP;
         e = hsk::launch_lse_reduce(planes, p->T * p->N, p->H, tau, tail, lse, s);
         if (e != hipSuccess) return HS_ERR_HIP;

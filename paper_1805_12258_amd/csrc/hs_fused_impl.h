@@ -112,15 +112,7 @@ template <> struct Io<bf16_t> {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
-// Compile-time loop: f(integral_constant<int, I>) for I = B..E.
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f)
-{
-    if constexpr (B <= E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + 1, E>(f);
-    }
-}
+using rows::static_for;
 
 // Shared-memory carve-up of one block.  The staging buffer and (when it
 // covers only one tile) the row table are double-buffered: the loads of the
@@ -129,9 +121,9 @@ struct Smem {
     float* stage[2];              // staged source rows of all m >= 2 (fp32); 16-bit
                                   // storage uses stage[0] only
     uint16_t* raw[2];             // 16-bit storage: raw staged halves (DMA targets)
-    float* rowtab[2];             // per row: staged-row offsets of m = 2..H, then
-                                  // the H thresholds (both entries alias when the
-                                  // table covers the whole plane)
+    float* rowtab[2];             // per row: staged-row offsets of m = 2..H (both
+                                  // entries alias when the table covers the whole
+                                  // plane)
     float* pairs;                 // [kWaves][H][2] the waves' pairs (log-sum-exp)
 };
 
@@ -398,8 +390,7 @@ __device__ __forceinline__ void issue_tile(const TileArgs& a, const RowGeo& g, i
         for (int q = 0; q < kRowsPerWave; ++q) {
             const int rr = wave + kWaves * q;
             const T* p = fop + (int64_t)(g.r0 + rr) * ld + jb;
-            // bins past the end start at -inf: no sum of them can pass a
-            // threshold (-inf + x is -inf or NaN)
+            // bins past the end are neither stored nor counted
 #pragma unroll
             for (int v = 0; v < kV; ++v)
                 Ld::put(x[q], v, (rr < g.nr && jb + v < N) ? Ld::bits(p + v) : Ld::kNegInf);
@@ -431,7 +422,7 @@ __device__ __forceinline__ void issue_tile(const TileArgs& a, const RowGeo& g, i
 }
 
 // Form the planes of one tile whose loads have completed (after a barrier):
-// HP_k for k = 1..H in the order of Eq. 2, detected or stored.
+// HP_k for k = 1..H in the order of Eq. 2, stored or taken into the statistic.
 template <typename TIn, int H, int MODE, bool FULL>
 __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g, int bt,
                                              const Smem& sh, const float* stage,
@@ -738,7 +729,8 @@ __device__ __forceinline__ void block_chunk(int64_t n, int64_t& t_begin, int64_t
 }
 
 // Detection (kModeDetect) walks the rows of bin tiles with every source value
-// in registers instead (hs_rows.h).
+// in registers instead (hs_rows.h), as k_walk does with four bins per lane; it
+// has no use for n_tiles.
 template <int MODE> struct ModeArgs {
     using T = TileArgs;
 };

@@ -23,7 +23,12 @@ constexpr int kThreads = kWaves * kLanes;
 constexpr int kRowsPerWave = 4;
 constexpr int kMaxTileRows = kWaves * kRowsPerWave;   // 32
 constexpr int kMaxH = 16;
-constexpr int kTailBytes = 20656;        // LDS a block has after its row table (the statistic's pairs)
+// LDS that a block of hs_sum and of the statistic reserves after its row table.
+// The statistic's pairs take at most 1 KB of it; with the rest a plan's lds_bytes
+// holds two blocks of five to thirteen planes to a compute unit (three would
+// fit without), and the resident grid is the one the statistic's partial sums
+// are formed over, whose order its last bits depend on.
+constexpr int kTailBytes = 20656;
 
 // Source words a tile needs per row of stretch factor m: the largest number
 // of distinct floor(j/m) over kTileBins consecutive bins starting at a
@@ -132,7 +137,7 @@ __host__ __device__ constexpr int dma_slot_regs(int H, int elem_bytes)
 }
 
 // Row table of a tile: per tile row, the staging offsets of stretch factors
-// 2..H (padded to 4 words) followed by the H thresholds (padded to 4).
+// 2..H (padded to 4 words), then H words (padded to 4) that hold zero.
 __host__ __device__ constexpr int row_table_thr_offset(int H) { return ((H - 1) + 3) & ~3; }
 __host__ __device__ constexpr int row_table_stride(int H)
 {

@@ -1,6 +1,6 @@
 // Strip-walk detection kernels for bf16 FOP storage, 4 bins per lane,
 // H = 9..12.
-#define HS_WALK_T walk::bf16
+#define HS_WALK_T bf16_t
 #define HS_WALK_NAME bf16
 #define HS_WALK_V 4
 #define HS_WALK_GROUP 2

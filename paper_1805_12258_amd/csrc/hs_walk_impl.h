@@ -19,11 +19,11 @@
 namespace hsk {
 namespace walk {
 
-constexpr int kWThrBytes = 16384;       // largest threshold table of a plan the strip walk takes
-
-struct bf16 {
-    uint16_t bits;
-};
+// Largest threshold table of a plan that the strip walk takes; taller planes
+// run as the tile kernel's strips of four bins per lane.  The walk itself has no
+// such limit: the line says which plans report the strip walk, and by which
+// pitch a batch rejects a FOP.
+constexpr int kWThrBytes = 16384;
 
 __host__ __device__ constexpr int thr_stride(int H) { return (H + 3) & ~3; }
 
