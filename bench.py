@@ -818,14 +818,16 @@ def main():
         log("variants done")
 
     if not args.no_variants:
-        # the fractional m/k mapping on the same plane (k source points per
-        # point of plane k, 36 at H = 8)
+        # the fractional m/k mapping on the same plane (plane k sums k source
+        # points per point, 36 over the planes of H = 8; the kernel gathers those
+        # of the planes above H/2, which hold the others': 26)
         pf = hs.Plan(T, N, H, mapping="fractional")
         rf = time_detect(pf, fop, ta, capacity, max(10, args.steps // 10), 3)
         abf = points * 4 + 8 * int(rf["counts"][-1]) + 8 * (H + 1)
         line["fractional"] = {"ms_per_step": rf["ms_per_step"], "launch_ms": rf["launch_ms"],
                               "value": points / (rf["ms_per_step"] * 1e-3), "unit": "points/s",
-                              "gathers_per_point": H * (H + 1) // 2, "candidates": int(rf["counts"][-1]),
+                              "terms_per_point": H * (H + 1) // 2,
+                              "gathers_per_point": sum(range(H // 2 + 1, H + 1)), "candidates": int(rf["counts"][-1]),
                               "hbm_gbs": abf / (rf["launch_ms"] * 1e-3) / 1e9,
                               "kernel": detection_kernel(pf)[0]}
         log("fractional: %.3f ms" % rf["ms_per_step"])

@@ -166,10 +166,10 @@ void even_runs(std::vector<Run> (&on)[8])
 // tiles for the tile kernel).  A single FOP spreads its strips over eight XCD
 // lists, a batch puts each FOP whole on one XCD (longest first onto the least
 // loaded XCD); the lists are then evened out.
-// Device layout: xseg [9] u32 | seg [n_seg][4] i32 | n_chans [n_fops] i64 |
-// entries u32 | tile schedule u32 (one buffer, so that a plan takes one
-// allocation and one copy).  `tiles`: the lists of the 256-bin tiles of a single
-// FOP, where they are those of the strips.
+// Device layout: seg [n_seg][4] i32 | n_chans [n_fops] i64 | entries u32 | tile
+// schedule u32 (one buffer, so that a plan takes one allocation and one copy).
+// `tiles`: the lists of the 256-bin tiles of a single FOP, where they are those
+// of the strips.
 void build_units(hs_plan* p, bool walk, bool linear, const std::vector<std::vector<uint32_t>>& tiles)
 {
     const int64_t sb = walk ? 64 * (int64_t)p->walk_v : hsk::kTileBins;
@@ -253,10 +253,9 @@ void build_units(hs_plan* p, bool walk, bool linear, const std::vector<std::vect
     }
 
     std::vector<int32_t> seg;   // 4 per segment: FOP, first entry, first index, end index
-    std::vector<uint32_t> xseg(9, 0);
     p->walk_units = 0;
     for (int x = 0; x < 8; ++x) {
-        xseg[x] = (uint32_t)(seg.size() / 4);
+        p->xseg[x] = (int32_t)(seg.size() / 4);
         int64_t pre = 0;
         for (const Run& r : on[x]) {
             seg.insert(seg.end(), {r.f, (int32_t)r.first, (int32_t)pre, (int32_t)(pre + r.count)});
@@ -264,11 +263,10 @@ void build_units(hs_plan* p, bool walk, bool linear, const std::vector<std::vect
         }
         p->walk_units = std::max(p->walk_units, pre);
     }
-    xseg[8] = (uint32_t)(seg.size() / 4);
+    p->xseg[8] = (int32_t)(seg.size() / 4);
 
     auto align = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    p->off_xseg = 0;
-    p->off_seg = align(p->off_xseg + xseg.size() * 4);
+    p->off_seg = 0;
     p->off_nchan = align(p->off_seg + seg.size() * 4);
     p->off_ent = align(p->off_nchan + nchan.size() * 8);
     p->off_sched = align(p->off_ent + ent.size() * 4);
@@ -276,7 +274,6 @@ void build_units(hs_plan* p, bool walk, bool linear, const std::vector<std::vect
     auto put = [&](size_t off, const auto& v) {
         if (!v.empty()) std::memcpy(p->tab.data() + off, v.data(), v.size() * sizeof(v[0]));
     };
-    put(p->off_xseg, xseg);
     put(p->off_seg, seg);
     put(p->off_nchan, nchan);
     put(p->off_ent, ent);
@@ -365,7 +362,7 @@ hsk::WalkArgs walk_args(const hs_plan* p, const unsigned char* tab)
     a.inv_scale = 1.0f / p->scale;
     a.s_row = p->s_row;
     a.s_bin = p->s_bin;
-    a.xseg = reinterpret_cast<const uint32_t*>(tab + p->off_xseg);
+    std::memcpy(a.xseg, p->xseg, sizeof(a.xseg));
     a.lists = p->lists;
     a.units_per_list = p->walk_units;
     std::memcpy(a.xfirst, p->xfirst, sizeof(a.xfirst));

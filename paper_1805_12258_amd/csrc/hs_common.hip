@@ -77,6 +77,7 @@ hipError_t launch_fused(int mode, int dtype, int H, const TileArgs& a, int64_t n
 hipError_t launch_tiles(int dtype, int H, const WalkArgs& a, int grid, hipStream_t s)
 {
     if (H < 1 || H > kMaxH) return hipErrorInvalidValue;
+    if (a.n_fops > 0) return launch_walk(dtype, H, kV, a, grid, s);   // the same strips
     switch (dtype) {
     case HS_DTYPE_F32: {
 #define HS_CALL(g) launch_tiles_f32_g##g(H, a, grid, s)

@@ -751,7 +751,7 @@ __global__ __launch_bounds__((fused_threads<H, MODE>()), (fused_min_waves<H, MOD
 {
     extern __shared__ __align__(16) float lds[];
     if constexpr (MODE == kModeDetect) {
-        rows::walk_plan<TIn, H, kV>(a, reinterpret_cast<unsigned char*>(lds));
+        rows::walk_plan<TIn, H, kV, false>(a, reinterpret_cast<unsigned char*>(lds));
     } else {
         constexpr int EB = sizeof(typename Io<TIn>::T);
         const Smem sh = carve<H, EB>(lds, a.T, a.R, a.table_whole != 0);
@@ -824,7 +824,7 @@ static hipError_t launch_fused_t(int mode, const TileArgs& a, int64_t n_tiles, i
     return hipGetLastError();
 }
 
-// Detection in 256-bin tiles.
+// Detection of a single FOP in 256-bin tiles.
 template <typename TIn, int H>
 static hipError_t launch_tiles_t(const WalkArgs& a, int grid, hipStream_t s)
 {

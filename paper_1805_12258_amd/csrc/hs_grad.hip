@@ -20,8 +20,8 @@
 // (m = 2, 4, 8, 16 by lanes alone).
 //
 // What bounds it.  The plain transpose: memory, 85 x 2^18 at H = 8 reads 713 MB
-// and writes 145 in 173 us of a training step (5.0 TB/s).  The statistic's:
-// the vector units, 32 exponentials (a quarter of the rate) and 350 other
+// and writes 149 in 173 us of a training step (5.0 TB/s).  The statistic's:
+// the vector units, 32 exponentials (a quarter of the rate) and 240 other
 // instructions per row of 256 bins: 85 x 2^20 230 to 250 us.  The second pass:
 // 19 and 79 us.  Both passes together, repeated, 168 and 312 us; tiles of rows
 // staged in LDS factor by factor, with a barrier each, and one point per

@@ -219,7 +219,7 @@ struct WalkArgs {
     int32_t s_row, s_bin;
     const uint32_t* ent;          // schedule entries: strips of 64 V bins
     const int32_t* seg;           // [n_seg][4]: FOP, first entry, first index, end index
-    const uint32_t* xseg;         // [9]: segments of XCD x are [xseg[x], xseg[x+1])
+    int32_t xseg[9];              // batch: segments of XCD x are [xseg[x], xseg[x+1])
     int32_t xfirst[8], xcount[8]; // single FOP: first entry and number of each XCD's strips
     int32_t lists;                // 8: a list per XCD; 1: one list that all XCDs take from
     int64_t units_per_list;       // strips of the longest list
@@ -334,9 +334,10 @@ struct hs_plan {
     bool walk = false;                   // the strip walk detects
     int walk_v = 4;                      // bins per lane (strips of 64 walk_v bins)
     std::vector<unsigned char> tab;
-    size_t off_xseg = 0, off_seg = 0, off_nchan = 0, off_ent = 0, off_sched = 0;
+    size_t off_seg = 0, off_nchan = 0, off_ent = 0, off_sched = 0;
     int lists = 8;                       // strip lists: one per XCD, or one for all
     int64_t walk_units = 0;              // strips of the longest list
+    int32_t xseg[9] = {0};               // batch: first segment of each XCD's
     int32_t xfirst[8] = {0}, xcount[8] = {0};   // single FOP: each XCD's strips
 
     // Device copies of `tab`, made on first use per device.

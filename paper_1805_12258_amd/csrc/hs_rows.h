@@ -9,7 +9,7 @@
 // of source row floor(i/m): at most two elements for V = 4 and four for
 // V = 8, one vector load per lane, selected per bin when the source row
 // changes and kept for the m rows that use it.  A row then costs V (H - 1)
-// adds, the maximum of the lane's sums per plane and one compare (83 vector
+// adds, the maximum of the lane's sums per plane and one compare (85 vector
 // instructions per row of 256 bins at H = 8).
 //
 // Loads.  The next source row of every factor is requested when the current
@@ -18,11 +18,11 @@
 // staging, no DMA and no counted wait.
 //
 // What bounds it (85 x 2^21, H = 8, fp32): the caches' traffic.  The L2s
-// fetch 1.55 planes (1.1 GB; 13 % of the requests hit, the sources of one
-// strip being read some 20 rows before or after its own rows), which at 165
-// us is 6.7 TB/s; the vector units are busy 58 % of the time.  The same plane
-// staged tile by tile through LDS took 208 us at four waves per SIMD (fp16:
-// 180 us, now 125; H = 16: 377 us, now 245).  Streaming loads outside the
+// fetch 1.53 planes (1.09 GB; 10 % of the requests hit, the sources of one
+// strip being read some 20 rows before or after its own rows), which at 172
+// us is 6.3 TB/s; vector instructions issue 63 % of the time.  The same plane
+// staged tile by tile through LDS took 215 us a call at four waves per SIMD,
+// 176 so (fp16 175 and 131; H = 16 355 and 250).  Streaming loads outside the
 // source quarter, two rows per step with everything requested two rows
 // earlier, and equal shares of rows instead of strips were not faster.
 //
@@ -263,6 +263,15 @@ __host__ __device__ static constexpr int block_waves(int H, int V) { return min_
 // Block bookkeeping of finish_block (ints).
 __host__ __device__ static constexpr int book_ints(int H, int W) { return (W * (H + 1) + 2 + 3) & ~3; }
 
+// A wave's place in a batch: its FOP, and the units of the list that are that
+// FOP's.
+struct state_t {
+    int64_t ld, ubeg, uend;
+    uintptr_t fop;
+    int32_t N, n, eoff, f;        // bins; strips; first entry; number, -1: none yet
+};
+static_assert(sizeof(state_t) % 16 == 0, "the table behind it is read 16 bytes at a time");
+
 // The row table covers the plane's rows once per block where it is small,
 // else the rows of each wave's piece (at most kOwnRows of them).
 constexpr int kTabBytes = 20 * 1024;
@@ -272,7 +281,7 @@ __host__ __device__ static constexpr int lds_bytes(int T, int H, int V)
 {
     const int W = block_waves(H, V);
     const int tab_rows = tab_whole(T, H) ? T + 2 : W * (kOwnRows + 2);
-    return W * cand_cap(V) * 8 + book_ints(H, W) * 4 + tab_rows * tab_stride(H) * 4;
+    return W * (cand_cap(V) * 8 + (int)sizeof(state_t)) + book_ints(H, W) * 4 + tab_rows * tab_stride(H) * 4;
 }
 
 // Blocks the device holds at once.
@@ -560,7 +569,7 @@ struct Walk {
 // upper ones, so that the source rows in use at one time are those of one
 // half.  The waves on an XCD take its units in turn (all waves those of the one
 // list of a plane of few strips).
-template <typename TIn, int H, int V>
+template <typename TIn, int H, int V, bool BATCH>
 __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem)
 {
     constexpr int EB = sizeof(TIn);
@@ -569,7 +578,8 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
     constexpr int HS = tab_stride(H);
     uint64_t* const cands = reinterpret_cast<uint64_t*>(smem);
     int* const book = reinterpret_cast<int*>(cands + W * cand_cap(VI));
-    float* tab = reinterpret_cast<float*>(book + book_ints(H, W));
+    state_t* const states = reinterpret_cast<state_t*>(book + book_ints(H, W));
+    float* tab = reinterpret_cast<float*>(states + W);
     const int wave = uni(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const bool whole = tab_whole(a.T, H);
@@ -577,11 +587,7 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
     const int xcd = shared ? 0 : blockIdx.x & 7;
     const int nw = (int)(shared ? gridDim.x : (gridDim.x - xcd + 7) >> 3) * W;       // waves on this list
     int64_t at = (int64_t)((int)(shared ? blockIdx.x : blockIdx.x >> 3) * W + wave) * a.run;
-    int turn = 0;                       // units of the run taken
     const int halves = a.c > 0 ? 2 : 1;
-    // first strip of a single FOP (its XCD lists are in the arguments),
-    // requested before the table is waited for
-    const int n1 = a.n_fops == 0 ? a.xcount[xcd] : 0;
     auto split = [&](int64_t u, int n, int& q, int& p) __attribute__((always_inline)) {
         const bool up = u >= (int64_t)n * a.pieces;
         if (up) u -= (int64_t)n * a.pieces;
@@ -589,11 +595,15 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
         p = uni((int)(u - (int64_t)q * a.pieces));
         return up;
     };
+    // first strip of a single FOP (its XCD lists are in the arguments),
+    // requested before the table is waited for
     int strip = -1;
-    if (at < (int64_t)n1 * halves * a.pieces) {
-        int q, p;
-        split(at, n1, q, p);
-        strip = (int)a.ent[a.xfirst[xcd] + q];
+    if constexpr (!BATCH) {
+        if (at < (int64_t)a.xcount[xcd] * halves * a.pieces) {
+            int q, p;
+            split(at, a.xcount[xcd], q, p);
+            strip = (int)a.ent[a.xfirst[xcd] + q];
+        }
     }
     if (whole) build_table<H>(tab, 0, a.T + 2, a.T, a.c, a.ta, a.scale, threadIdx.x, 64 * W);
     else tab += wave * (kOwnRows + 2) * HS;
@@ -615,44 +625,45 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
             w.unit(fop, ld, N, a.c, (int)j, r0, r1, tab, whole ? 0 : r0);
     };
 
-    // one loop over both kinds of unit list, so that the walk is there once
-    int s = 0, s_end = 0, cur = -1;
-    int64_t ld = a.ld;
-    int N = a.N, n = n1, eoff = a.xfirst[xcd];
-    int64_t ubeg = 0, uend = (int64_t)n1 * halves * a.pieces;
-    gptr_t fop = (gptr_t)a.fop;
-    bool ok = true;
-    if (a.n_fops == 0) {
+    if constexpr (!BATCH) {
         w.sink = Sink{a.out, a.cap, a.counts};
-    } else {
-        s = uni((int)a.xseg[xcd]);
-        s_end = uni((int)a.xseg[xcd + 1]);
+        const int n = a.xcount[xcd];
+        const int64_t units = (int64_t)n * halves * a.pieces;
+        for (; at < units; at = uni64(at + nw)) {
+            w.n = uni(w.n);
+            int q, p;
+            const bool up = split(at, n, q, p);
+            if (strip < 0) strip = uni((int)a.ent[a.xfirst[xcd] + q]);
+            one((gptr_t)a.fop, a.ld, a.N, up, p, (uint32_t)strip);
+            strip = -1;
+        }
+        w.finish_block(book);
+        return;
     }
+
+    // what the wave needs to know of its FOP lies in LDS from unit to unit: the
+    // walk has no scalar registers to spare
+    states[wave] = state_t{0, 0, 0, 0, 0, 0, 0, -1};
     for (;;) {
         // wave-uniform loop state, stated as such for the compiler
-        s = uni(s);
-        cur = uni(cur);
-        n = uni(n);
-        eoff = uni(eoff);
-        N = uni(N);
-        ld = uni64(ld);
-        fop = (gptr_t)(uintptr_t)uni64((int64_t)(uintptr_t)fop);
-        ubeg = uni64(ubeg);
-        uend = uni64(uend);
         at = uni64(at);
         w.n = uni(w.n);
-        if (at >= uend) {
-            // the segment of the list that holds the unit (batch): FOP, first
-            // entry, first and end index.  Many short FOPs lie between two
-            // units of a wave, so 64 segments are looked at in one step (5000
-            // FOPs of 9 x 100 bins 387 us one after another, 31 so)
-            int lo = s, hi = s_end, step = 1, before = 0;
+        asm volatile("" ::: "memory");
+        state_t& st = states[opaque_s(wave)];
+        const state_t now = st;         // (all of it requested before any is waited for)
+        if (at >= uni64(now.uend)) {
+            // the segment of the list that holds the unit: FOP, first entry,
+            // first and end index.  Many short FOPs lie between two units of a
+            // wave, so 64 segments are looked at in one step (5000 FOPs of 9 x
+            // 100 bins 387 us one after another, 31 so)
+            int lo = a.xseg[xcd], hi = a.xseg[xcd + 1], step = 1, before = 0;
             seg_t g;
+            const int l = opaque(lane);
             do {
                 const int left = uni(hi - lo);
                 if (left <= 0) break;
                 step = (left + 63) >> 6;
-                const int i = lo + (lane + 1) * step - 1;
+                const int i = lo + (l + 1) * step - 1;
                 g = reinterpret_cast<const seg_t*>(a.seg)[min(i, hi - 1)];
                 const bool past = i < hi && (int64_t)g.w * halves * a.pieces <= at;
                 before = uni(__builtin_popcountll(__builtin_amdgcn_ballot_w64(past)));
@@ -661,48 +672,42 @@ __device__ __forceinline__ void walk_plan(const WalkArgs& a, unsigned char* smem
             } while (step > 1);
             if (lo >= hi) break;
             const int f = __builtin_amdgcn_readlane(g.x, before);
-            eoff = __builtin_amdgcn_readlane(g.y, before);
-            const int i0 = __builtin_amdgcn_readlane(g.z, before);
-            n = __builtin_amdgcn_readlane(g.w, before) - i0;
-            ubeg = (int64_t)i0 * halves * a.pieces;
-            uend = ubeg + (int64_t)n * halves * a.pieces;
-            s = lo + 1;
+            const int i0 = __builtin_amdgcn_readlane(g.z, before), n = __builtin_amdgcn_readlane(g.w, before) - i0;
+            const int64_t ubeg = (int64_t)i0 * halves * a.pieces;
+            const int cur = uni(now.f);
+            st.eoff = __builtin_amdgcn_readlane(g.y, before);
+            st.n = n;
+            st.ubeg = ubeg;
+            st.uend = ubeg + (int64_t)n * halves * a.pieces;
             if (f == cur) continue;
-            if (cur >= 0 && ok) w.finish_wave();
-            cur = f;
+            if (cur >= 0 && w.sink.counts) w.finish_wave();
             const uintptr_t fp = (uintptr_t)uni64((int64_t)(uintptr_t)a.fops[f]);
-            N = uni((int)a.n_chans[f]);
-            ld = uni64(a.lds[f]);
-            fop = (gptr_t)fp;
+            const int N = uni((int)a.n_chans[f]);
+            const int64_t ld = uni64(a.lds[f]);
+            st.f = f;
+            st.N = N;
+            st.ld = ld;
+            st.fop = fp;
             // a FOP whose address or pitch breaks the alignment rules is
-            // skipped, its total set to -1
-            ok = (fp & 15) == 0 && ld % (16 / EB) == 0 && ld >= N &&
-                 ((uint64_t)ld * (uint64_t)a.lim_rows + (uint64_t)a.lim_bins) * EB <= 0xffffffffull;
+            // skipped (no counts to add to), its total set to -1
+            const bool ok = (fp & 15) == 0 && ld % (16 / EB) == 0 && ld >= N &&
+                            ((uint64_t)ld * (uint64_t)a.lim_rows + (uint64_t)a.lim_bins) * EB <= 0xffffffffull;
             unsigned long long* const cn = a.counts + (int64_t)f * (H + 1);
-            w.sink = Sink{a.out + uni64(a.out_offsets[f]), uni64(a.caps[f]), cn};
-            if (!ok && lane == 0) cn[H] = ~0ull;
+            w.sink = Sink{a.out + uni64(a.out_offsets[f]), uni64(a.caps[f]), ok ? cn : nullptr};
+            if (!ok && l == 0) cn[H] = ~0ull;
             continue;
         }
-        if (ok) {
+        if (w.sink.counts) {
             int q, p;
-            const bool up = split(at - ubeg, n, q, p);
-            if (strip < 0) strip = uni((int)a.ent[eoff + q]);
-            one(fop, ld, N, up, p, (uint32_t)strip);
-            strip = -1;
+            const bool up = split(at - uni64(now.ubeg), uni(now.n), q, p);
+            const uint32_t e = (uint32_t)uni((int)a.ent[uni(now.eoff) + q]);
+            one((gptr_t)(uintptr_t)uni64((int64_t)now.fop), uni64(now.ld), uni(now.N), up, p, e);
         }
-        turn = uni(turn + 1);
         at += 1;
-        if (turn == a.run) {
-            at += (int64_t)(nw - 1) * a.run;
-            turn = 0;
-        }
+        if (((int)at & (a.run - 1)) == 0) at += (int64_t)(nw - 1) * a.run;
     }
-    // batched: waves may end on different FOPs
-    if (a.n_fops > 0) {
-        if (cur >= 0 && ok) w.finish_wave();
-    } else {
-        w.finish_block(book);
-    }
+    // waves may end on different FOPs
+    if (uni(states[wave].f) >= 0 && w.sink.counts) w.finish_wave();
 }
 
 // Pieces a half strip's rows are cut into, for `strips` strips on `waves`

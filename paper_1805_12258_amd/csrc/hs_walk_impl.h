@@ -34,13 +34,23 @@ __global__ __launch_bounds__((64 * rows::block_waves(H, rows::lane_bins(H, V))),
                              (rows::min_waves(H, rows::lane_bins(H, V)))) void k_walk(WalkArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    rows::walk_plan<TIn, H, V>(a, smem);
+    rows::walk_plan<TIn, H, V, false>(a, smem);
+}
+
+// The same over a batch (a kernel of its own: the walk has no scalar registers
+// to spare for a batch's place in its list where there is none).
+template <typename TIn, int H, int V>
+__global__ __launch_bounds__((64 * rows::block_waves(H, rows::lane_bins(H, V))),
+                             (rows::min_waves(H, rows::lane_bins(H, V)))) void k_walk_batch(WalkArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    rows::walk_plan<TIn, H, V, true>(a, smem);
 }
 
 template <typename TIn, int H, int V>
 hipError_t launch_walk_t(const WalkArgs& a, int grid, hipStream_t s)
 {
-    return rows::launch_plan(k_walk<TIn, H, V>, H, V, a, grid, s);
+    return rows::launch_plan(a.n_fops > 0 ? k_walk_batch<TIn, H, V> : k_walk<TIn, H, V>, H, V, a, grid, s);
 }
 
 }  // namespace hsk
