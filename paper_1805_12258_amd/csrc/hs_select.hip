@@ -154,6 +154,14 @@ __device__ __forceinline__ int range_shift(uint64_t lo, uint64_t hi, int bins)
     return span < (uint64_t)bins ? 0 : (64 - lb) - __builtin_clzll(span);
 }
 
+// Last key of the bin of width 2^shift that begins at lo <= hi, within a range
+// that ends at hi (the uppermost bin of a range may end past 2^64).
+__device__ __forceinline__ uint64_t bin_end(uint64_t lo, int shift, uint64_t hi)
+{
+    const uint64_t w = (((uint64_t)1) << shift) - 1;
+    return hi - lo < w ? hi : lo + w;
+}
+
 // Per-plane summary shared by the passes.
 struct alignas(128) PlaneInfo {   // one cache line each: the passes' atomics on different planes do not meet
     uint64_t lo, hi;          // key range of the plane
@@ -514,8 +522,7 @@ __global__ __launch_bounds__(kST) void k_sel_final(const uint64_t* __restrict__ 
     // the boundary entries lie in [lo, hi]; split further while they do not
     // fit in LDS (keys are distinct, so each round narrows the range)
     uint64_t lo = pi.lo + ((uint64_t)(pi.cut < 0 ? 0 : pi.cut) << pi.shift);
-    uint64_t hi = lo + ((((uint64_t)1) << pi.shift) - 1);
-    hi = hi < pi.hi ? hi : pi.hi;
+    uint64_t hi = bin_end(lo, pi.shift, pi.hi);
     int64_t in_range = m;
     while (need > 0 && in_range > kSelLdsBnd) {
         if (hi - lo < 1024) break;   // one key per bin already (only repeated entries get here)
@@ -560,10 +567,8 @@ __global__ __launch_bounds__(kST) void k_sel_final(const uint64_t* __restrict__ 
         __syncthreads();
         need -= above_s;
         in_range = inbin_s;
-        const uint64_t nlo = lo + ((uint64_t)cut << shift);
-        const uint64_t nhi = nlo + ((((uint64_t)1) << shift) - 1);
-        lo = nlo;
-        hi = nhi < hi ? nhi : hi;
+        lo += (uint64_t)cut << shift;
+        hi = bin_end(lo, shift, hi);
         __syncthreads();
     }
     if (need > 0) {
