@@ -22,9 +22,9 @@
 // strip, then strips follow one another on an XCD, so that the source rows of
 // neighbours and of the chains (all read m = K) meet in its L2.
 //
-// What bounds it: the L1's access rate (14 accesses per unaligned vector load
+// What bounds it: the L1's access rate (13 accesses per unaligned vector load
 // of a wave, which keeping the sources saves 44 % of) and, as much, the
-// caches' traffic: 85 x 2^19, H = 8, fp32 fetches 1.0 GB (5.7 planes) in 207
+// caches' traffic: 85 x 2^19, H = 8, fp32 fetches 1.37 GB (7.7 planes) in 207
 // us.  One load per bin and term took 817 us (fp16, 2^18 bins: 504 us, now 84;
 // H = 16 fp16 2^18: 1790 us, now 292; 127 x 2^20 at H = 4: 1176 us, now 198).
 //

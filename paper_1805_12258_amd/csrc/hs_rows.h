@@ -9,7 +9,7 @@
 // of source row floor(i/m): at most two elements for V = 4 and four for
 // V = 8, one vector load per lane, selected per bin when the source row
 // changes and kept for the m rows that use it.  A row then costs V (H - 1)
-// adds, the maximum of the lane's sums per plane and one compare (85 vector
+// adds, the maximum of the lane's sums per plane and one compare (82 vector
 // instructions per row of 256 bins at H = 8).
 //
 // Loads.  The next source row of every factor is requested when the current
@@ -18,9 +18,9 @@
 // staging, no DMA and no counted wait.
 //
 // What bounds it (85 x 2^21, H = 8, fp32): the caches' traffic.  The L2s
-// fetch 1.53 planes (1.09 GB; 10 % of the requests hit, the sources of one
-// strip being read some 20 rows before or after its own rows), which at 172
-// us is 6.3 TB/s; vector instructions issue 63 % of the time.  The same plane
+// fetch 1.51 planes (1.08 GB; 10 % of the requests hit, the sources of one
+// strip being read some 20 rows before or after its own rows), which at 169
+// us is 6.4 TB/s; vector instructions issue 62 % of the time.  The same plane
 // staged tile by tile through LDS took 215 us a call at four waves per SIMD,
 // 176 so (fp16 175 and 131; H = 16 355 and 250).  Streaming loads outside the
 // source quarter, two rows per step with everything requested two rows
