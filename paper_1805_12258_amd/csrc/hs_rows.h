@@ -37,6 +37,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "hs_internal.h"
@@ -284,15 +285,15 @@ __host__ __device__ static constexpr int lds_bytes(int T, int H, int V)
     return W * (cand_cap(V) * 8 + (int)sizeof(state_t)) + book_ints(H, W) * 4 + tab_rows * tab_stride(H) * 4;
 }
 
-// Blocks the device holds at once.
-static inline int resident_blocks(const void* k, int threads, int lds)
+// Blocks the device holds at once, at most so many per compute unit.
+static inline int resident_blocks(const void* k, int threads, int lds, int most = INT32_MAX)
 {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-    return cus * per_cu;
+    return cus * std::min(per_cu, most);
 }
 
 // Where a wave's candidates go.
@@ -746,7 +747,10 @@ static hipError_t launch_plan(void (*k)(WalkArgs, A...), int H, int V, WalkArgs 
     const int W = block_waves(H, VI);
     const int lds = lds_bytes(a.T, H, VI);
     (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (grid <= 0) grid = resident_blocks((const void*)k, 64 * W, lds);
+    // the waves the kernel is compiled for, also where few planes leave registers
+    // for more: 1024 blocks for 768 cost 85 x 2^18 fp32 at two planes 40 us for
+    // 34 (their atomics at the end)
+    if (grid <= 0) grid = resident_blocks((const void*)k, 64 * W, lds, 4 * min_waves(H, VI) / W);
     if (grid < a.lists) grid = a.lists;   // every list needs a block
     a.pieces = row_pieces(a.lists * a.units_per_list, a.T, (int64_t)grid * W, tab_whole(a.T, H));
     const int halves = a.T > 1 ? 2 : 1;
