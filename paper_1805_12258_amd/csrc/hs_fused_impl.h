@@ -497,11 +497,13 @@ __device__ __forceinline__ void compute_tile(const TileArgs& a, const RowGeo& g,
                 float o[kV];
 #pragma unroll
                 for (int v = 0; v < kV; ++v) o[v] = Scaled<TIn>::value ? acc[v] * a.inv_scale : acc[v];
-                if constexpr (FULL) {
-                    // one store whatever N is: 4-byte aligned (85 x 2^19 at
-                    // H = 8 365 -> 345 us, 128 x 300001 with a store per bin
-                    // 786 -> 490, 64 x 100003 at H = 5 66 -> 37)
-                    typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+                // one store whatever N is: 4-byte aligned (85 x 2^19 at
+                // H = 8 365 -> 345 us, 128 x 300001 with a store per bin
+                // 786 -> 490, 64 x 100003 at H = 5 66 -> 37); in the ragged
+                // tile too, but for the lane at the end (20000 x 992 at H = 16
+                // 504 -> 350 us, where storing per bin also cost the full tiles)
+                typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+                if (FULL || jb + kV <= N) {
                     *reinterpret_cast<float4_a4*>(dst) = float4_a4{o[0], o[1], o[2], o[3]};
                 } else {
 #pragma unroll
