@@ -579,6 +579,34 @@ __device__ __forceinline__ void sort_bucket(uint64_t* __restrict__ out, const Pl
         if (place_of<K>(q) < m) out[place_of<K>(q)] = x[q];
 }
 
+// A small bucket (m <= NT): each entry's word is compared with all others, which no
+// crowd of words slows down.  False, with nothing written, where two are equal.
+template <int NT>
+__device__ __forceinline__ bool rank_all(uint64_t* __restrict__ out, const Placed* __restrict__ in, int m,
+                                         unsigned char* smem)
+{
+    typedef uint32_t four __attribute__((ext_vector_type(4), may_alias));
+    uint32_t* const word = reinterpret_cast<uint32_t*>(smem);
+    uint32_t* const given = word + NT;
+    const int t = threadIdx.x;
+    const uint64_t x = in[t < m ? t : 0].e;
+    const uint32_t w = (uint32_t)x;
+    word[t] = t < m ? w : ~0u;          // past the end: below no word
+    given[t] = 0;
+    __syncthreads();
+    int rank = 0;
+    if (t < m) {
+        for (int e = 0; e < m; e += 4) {
+            const four y = *reinterpret_cast<const four*>(word + e);
+            rank += (y.x < w ? 1 : 0) + (y.y < w ? 1 : 0) + (y.z < w ? 1 : 0) + (y.w < w ? 1 : 0);
+        }
+    }
+    // equal words get the same rank
+    if (__syncthreads_or(t < m && atomicAdd(&given[rank], 1u) > 0)) return false;
+    if (t < m) out[rank] = x;
+    return true;
+}
+
 template <int NT>
 __global__ __launch_bounds__(NT, 4) void k_sort_buckets(uint64_t* __restrict__ cand,
                                                           const uint32_t* __restrict__ start,
@@ -590,6 +618,10 @@ __global__ __launch_bounds__(NT, 4) void k_sort_buckets(uint64_t* __restrict__ c
     if (m == 0) return;
     uint64_t* const out = cand + first;
     Placed* const in = placed + first;
+    // the 64 buckets of a short list: 2500 entries 15.5 -> 14.7 us, 9000 at log-
+    // uniform bins 22 -> 20, 9000 in one row 31 -> 29 (buckets of up to 512 so:
+    // 16 384 entries 24 -> 27)
+    if (NT == kBTh / 2 && m <= NT && rank_all<NT>(out, in, m, smem)) return;
     if (m <= NT) return sort_bucket<NT, 1>(out, in, m, smem);
     if (m <= 2 * NT) return sort_bucket<NT, 2>(out, in, m, smem);
     if (m <= 4 * NT) return sort_bucket<NT, 4>(out, in, m, smem);
