@@ -104,17 +104,28 @@ def test_time_does_not_depend_on_the_words(n):
     assert max(us.values()) <= 4 * us["spread"]
 
 
-def test_time_of_crowded_bins_in_a_short_list(monkeypatch):
+def test_time_of_crowded_bins_in_a_short_list():
     """9000 different entries at log-uniform bins against evenly spread bins: 1.14
-    times the time where entries are ranked inside bins, 1.0 against all others."""
-    def different(kind):
-        def words(n, rng):
-            w = np.unique(np.concatenate([kind(2 * n, rng), kind(2 * n, rng)]))
-            return rng.permutation(w)[:n]
-        return words
+    times the time where entries are ranked inside bins, 1.0 against all others.
+    The two in turn (a clock that rises favours neither), the smallest of each."""
+    n, src, us = 9000, {}, {}
     for k in ("rednoise", "fields"):
-        monkeypatch.setitem(KINDS, k + ", different", different(KINDS[k]))
-    us = {k: min(sort_us(k + ", different", 9000) for _ in range(6)) for k in ("rednoise", "fields")}
+        rng = np.random.default_rng(n)
+        w = rng.permutation(np.unique(np.concatenate([KINDS[k](2 * n, rng), KINDS[k](2 * n, rng)])))[:n]
+        src[k] = torch.from_numpy(np.stack([w, np.arange(n, dtype=np.uint32)], axis=1).view(np.int32)).cuda()
+        us[k] = float("inf")
+    dev = torch.empty_like(src["fields"])
+    work = torch.empty(hs.hs_sort_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    for i in range(300):
+        for k in src:
+            dev.copy_(src[k])
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            hs.hs_sort_candidates(dev, n, work)
+            e1.record()
+            e1.synchronize()
+            if i >= 50:
+                us[k] = min(us[k], 1e3 * e0.elapsed_time(e1))
     print("case", us, flush=True)
     assert us["rednoise"] <= 1.08 * us["fields"], us
 
